@@ -1074,7 +1074,9 @@ bte_status enqueue_sweep(bte_ctx* h, bool adj, int nacc, int mode, int force, hi
   a.grp_t = adj ? h->d_gt_a : h->d_gt_f;
   a.force = force;
   if (h->dim < 3 || h->l3r) {
-    const size_t lds = (size_t)a.lds_stage + (size_t)std::max(2, nacc) * h->lds_stage_plane;
+    // one ordinate per lane stages one plane, double-buffered, whatever nacc
+    const int planes = h->plan.G == 1 ? 2 : std::max(2, nacc);
+    const size_t lds = (size_t)a.lds_stage + (size_t)planes * h->lds_stage_plane;
     if (h->l3r)
       HIPCHK(launch_sweep3r(h->precision, h->plan.NR, h->plan.P, nacc, mode, a, h->grid, h->block, lds, st));
     else

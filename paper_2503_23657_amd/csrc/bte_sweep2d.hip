@@ -31,9 +31,10 @@
 //   * the P waves of a workgroup sweep P ordinate groups of one octant in
 //     lockstep; per step each wave stages its per-row sums over its G ordinates
 //     in LDS, and the P partials of every cell are added in a fixed order and
-//     written as contiguous row segments: for the temperature-only sweep
-//     (double-buffered staging, one barrier per chunk) during the next chunk's
-//     steps, otherwise after the chunk;
+//     written as contiguous row segments: with one staged plane (temperature
+//     sums only, or one ordinate per lane, whose other sums are multiples of
+//     it; double-buffered staging, one barrier per chunk) during the next
+//     chunk's steps, otherwise after the chunk;
 //   * chunks run in runs of one kind (no boundary entries / x- and row-0
 //     y-inflows / any inflow), each kind in a loop of its own, so that the
 //     registers of the prefetch ring stay in place from chunk to chunk;
@@ -132,6 +133,8 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
   using namespace s2d;
   static_assert(!L3 || (NR <= 2 && G == 1), "3D rows-per-lane: NR <= 2, one ordinate per lane");
   static_assert(MODE != M2_SECOND || G == 1, "second-order faces: one ordinate per lane");
+  constexpr bool PS = G == 1;                   // the lane carries its weighted variable (below)
+  constexpr int SP = PS ? 1 : NACC;             // planes staged per step
   constexpr int RB = L3 ? F3_ROW_BITS : F2_ROW_BITS;  // flag bits per row
   constexpr unsigned B_ACT = L3 ? F3_ACT : F2_ACT;
   constexpr unsigned B_INX = L3 ? F3_INX : F2_INX;
@@ -226,7 +229,6 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
     // in the temperature sum (the recurrence is linear), so that sum needs no
     // multiply; what enters f is scaled by w0 and what is read from it by
     // 1 / w0 (a padding ordinate has w0 = 0: its lanes carry 0)
-    constexpr bool PS = G == 1;
     double tg_scale = 1.0;
     if constexpr (PS) {
       const T w0 = wacc[0][0];
@@ -470,26 +472,53 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
     //      thread takes whole (lane, step) pairs: pair e -> lane e/8, step e%8,
     //      so 8 neighbouring threads write 8 consecutive cells of each of the
     //      lane's rows; the NR rows of a pair are one vector read per wave.
-    //      Temperature-only sweeps (NACC == 1, double-buffered staging) write a
+    //      Sweeps that stage one plane (SP == 1, double-buffered) write a
     //      chunk out during the next chunk's steps, a batch of pairs read at
     //      an even step and stored at the odd step after it, so no step waits
     //      on LDS and the stores need no wait at all.
-    constexpr bool PIPE = NACC == 1;
+    //      With one ordinate per lane a wave's other sums are its staged
+    //      temperature sum times a constant of the wave (the ordinate's flux
+    //      or dJ/dQ weight over its temperature weight), so one plane is
+    //      staged and the write-out forms every plane's sum from it.
+    constexpr bool PIPE = SP == 1;
     constexpr int PAIRS = kC2 / P;
     constexpr int NB = PIPE ? (PAIRS < kC2 / 2 ? PAIRS : kC2 / 2) : 1;
     // pairs per batch: the pipelined write-out splits the pairs over NB
     // batches; the chunk-end write-out takes a power of two (so it divides
     // PAIRS) that keeps a batch's reads within ~32 registers
     constexpr int MB = PIPE ? PAIRS / NB
-                            : pow2_floor(min_c(PAIRS, 32 / (NACC * NR * (int)(sizeof(T) / 4))));
+                            : pow2_floor(min_c(PAIRS, 32 / (SP * NR * (int)(sizeof(T) / 4))));
     static_assert(MB >= 1 && PAIRS % MB == 0 && (!PIPE || MB * NB == PAIRS),
                   "write-out batches must tile the pairs exactly");
     const int t_wo = p * 64 + lane;
     int wvv[MB];
+    // the constants of the P waves' ordinates: in registers while there are
+    // few, else one per lane of a register and taken with readlane
+    constexpr int NWQ = PS && NACC > 1 ? (NACC - 1) * P : 0;
+    constexpr bool WQ_LANES = NWQ * (int)sizeof(T) / 4 > 12;
+    T wq[NWQ > 0 ? NWQ : 1], wql = T(0);
+    if constexpr (NWQ > 0) {
+#pragma unroll
+      for (int q = 0; q < P; ++q) {
+        const CAS T* gq = cp(reinterpret_cast<const T*>(A.grp_t)) + (size_t)(jd.grp + q) * GS;
+        const T w0 = gq[go_wacc(G, 0)];
+        const T iw = w0 > T(0) ? T(1) / w0 : T(0);
+#pragma unroll
+        for (int a = 1; a < NACC; ++a) {
+          const T w = gq[go_wacc(G, a)] * iw;
+          if constexpr (WQ_LANES) wql = lane == (a - 1) * P + q ? w : wql;
+          else wq[(a - 1) * P + q] = w;
+        }
+      }
+    }
+    auto wconst = [&](int a, int q) BTE_INL {
+      if constexpr (WQ_LANES) return rdlane(wql, (a - 1) * P + q);
+      else return wq[(a - 1) * P + q];
+    };
     // the pipelined write-out holds every wave's partial until the store step
     // (its adds then wait on nothing); the chunk-end one adds as it reads
     constexpr int PQ = PIPE ? P : 1;
-    VR wraw[NACC][MB][PQ];
+    VR wraw[SP][MB][PQ];
     // read a batch of pairs of chunk chw (its records and every wave's sums)
     auto wo_read = [&](int b, int chw) BTE_INL {
       const int bw = chw & 1;
@@ -500,8 +529,8 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
         const int ln = e >> 3, cc = e & 7;
         wvv[mi] = scr[cc * CS + ln];
 #pragma unroll
-        for (int a = 0; a < NACC; ++a) {
-          const T* sp = stage + (size_t)(NACC == 1 ? bw : a) * plane_sz + (size_t)r * kC2 * RS + cc * RS + ln * NR;
+        for (int a = 0; a < SP; ++a) {
+          const T* sp = stage + (size_t)(PIPE ? bw : a) * plane_sz + (size_t)r * kC2 * RS + cc * RS + ln * NR;
           if constexpr (PIPE) {
 #pragma unroll
             for (int q = 0; q < P; ++q) wraw[a][mi][q] = *reinterpret_cast<const VR*>(sp + (size_t)q * R * kC2 * RS);
@@ -522,9 +551,19 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
         const int cid0 = v >> 5;
 #pragma unroll
         for (int a = 0; a < NACC; ++a) {
-          VR sm = wraw[a][mi][0];
+          VR sm = wraw[PS ? 0 : a][mi][0];
+          if (PS && a > 0) {
+            sm *= wconst(a, 0);
 #pragma unroll
-          for (int q = 1; q < PQ; ++q) sm += wraw[a][mi][q];
+            for (int q = 1; q < PQ; ++q) {
+              const T w = wconst(a, q);
+#pragma unroll
+              for (int k = 0; k < NR; ++k) sm[k] = fma(w, wraw[0][mi][q][k], sm[k]);
+            }
+          } else {
+#pragma unroll
+            for (int q = 1; q < PQ; ++q) sm += wraw[PS ? 0 : a][mi][q];
+          }
           if constexpr (!L3) {
             // 1D/2D planes keep one job per group: the cell index itself. The
             // lane axis is the grid's slowest, so a row of the lane outside
@@ -575,7 +614,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
       och = OCH[0];
     }
     auto emit = [&](int c) BTE_INL {
-      const T* sb = stage + (size_t)(NACC == 1 ? (c & 1) : 0) * plane_sz + (size_t)(p * R + r) * kC2 * RS;
+      const T* sb = stage + (size_t)(PIPE ? (c & 1) : 0) * plane_sz + (size_t)(p * R + r) * kC2 * RS;
       // the axis weight of an entry by arithmetic (a select between the
       // three would be turned into an indexed read of a stack copy)
       const T wA = wo0[0], wB = wo1[0] - wo0[0], wC = wo2[0] - wo1[0];
@@ -602,7 +641,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
       constexpr bool XS = decltype(xs_tag)::value && !L3;  // 3D: every inflow goes through the stream
       const int bufi = ch & 1;
       const T* inbuf = my_inb + bufi * E;
-      T* stg0 = stage + (size_t)(NACC == 1 ? bufi : 0) * plane_sz + (size_t)(p * R + r) * kC2 * RS;
+      T* stg0 = stage + (size_t)(PIPE ? bufi : 0) * plane_sz + (size_t)(p * R + r) * kC2 * RS;
       int* scw = scid + (bufi * R + r) * kC2 * CS;
       int out_cnt = 0;
       // the chunk's prefetch: 3D through the fixed views with a uniform offset
@@ -795,7 +834,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
 
         // ---- fused band/direction sums of the rows, staged for the workgroup
 #pragma unroll
-        for (int a = 0; a < NACC; ++a) {
+        for (int a = 0; a < SP; ++a) {
           VR acc;
 #pragma unroll
           for (int k = 0; k < NR; ++k) {
@@ -804,7 +843,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
             for (int g = 0; g < G; ++g) sm = (PS && a == 0) ? f[g][k] : fma(wacc[a][g], f[g][k], sm);
             acc[k] = sm;
           }
-          *reinterpret_cast<VR*>(stg0 + (size_t)(NACC == 1 ? 0 : a) * plane_sz + u * RS + lane * NR) = acc;
+          *reinterpret_cast<VR*>(stg0 + (size_t)(PIPE ? 0 : a) * plane_sz + u * RS + lane * NR) = acc;
         }
         scw[u * CS + lane] = rec.x;  // every wave of the slot writes the same records
 
@@ -877,7 +916,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
             }
         }
 
-        // ---- the previous chunk's write-out (temperature-only sweeps)
+        // ---- the previous chunk's write-out
         if constexpr (PIPE) {
           if (u % 2 == 0 && u / 2 < NB) wo_read(u / 2, ch - 1);
           if (u % 2 == 1 && u / 2 < NB) wo_store(ch > 0);
