@@ -149,7 +149,9 @@ struct Inst {
   void* d_xqa[2] = {nullptr, nullptr};
   void* d_outv = nullptr;
   void* d_part = nullptr;
-  int part_ld = 0;  // cells per job in a partial-sum plane (ncell padded to cell blocks)
+  int n_part = 0;   // indices of a partial-sum plane (cells, and the padding of its blocks)
+  int* d_cell_of = nullptr;  // [n_part] cell of each plane index (NULL: itself)
+  int part_ld = 0;  // cells per job in a partial-sum plane (n_part padded to cell blocks)
   int part_jg = 0;  // log2 of the jobs per group of a plane
   void* d_store = nullptr;
   double* d_tgrad = nullptr;
@@ -194,6 +196,10 @@ struct bte_ctx {
   size_t ws_cap = 0;
   bool ws_store = false;               // the bound workspace holds the adjoint's angular field
   size_t need_static = 0, need_plan = 0, need_store = 0;  // workspace bytes of the current plan
+  bool part_blocks = true;             // order of the cells in the partial-sum planes (see plane_order)
+  Plan part_plan;                      // plan and order it was chosen for (order 0: none yet)
+  int part_order = 0;
+  long long part_extra = 0, store_extra = 0;  // bytes that order adds to need_plan and need_store
   GroupSet gs;                         // ordinate groups of the current plan
   Plan sched_plan;                     // plan the host schedules were built for
   bool sched_valid = false;
@@ -304,9 +310,35 @@ std::vector<double> corr_coefficients(const bte_ctx* h, const HostInst& hi) {
   return out;
 }
 
+// Order of the cells in a rows-per-lane layout's partial-sum planes: blocks of
+// kC2 columns of the step axis (padded to whole blocks), in a block plane after
+// plane and row after row, a row's kC2 columns side by side. A wave writes a
+// chunk's kC2 columns of 64 lanes at a time, so the 128-byte lines of a plane
+// fill within two chunks; in grid order a line waited for the next block of
+// columns (3D: a whole block of planes later) and left the L2 in 32-byte
+// pieces once the open lines of every workgroup outgrew it (flux sweep of the
+// 96x96x120 FinFET-like domain: 8.8 GB written for 4.2 GB of sums; of the 256^2
+// square: 515 MB for 189 MB). 24 iterations of the FinFET-like domain went from
+// 113.1 to 93.3 ms with it, the square's solve from 9.33 to 9.05 ms. In 1D/2D
+// the rows are padded to whole lanes, so a lane's rows past the grid need no
+// mask.
+PlaneOrder plane_order(const HostInst& hi, const Schedule& S) {
+  const bool d3 = hi.dim == 3;
+  const int ax[3] = {d3 ? S.ax[0] : 0, d3 ? S.ax[1] : 1, d3 ? S.ax[2] : 2};
+  const int st[3] = {1, hi.n[0], hi.n[0] * hi.n[1]};
+  PlaneOrder po;
+  for (int e = 0; e < 3; ++e) {
+    po.n[e] = hi.n[ax[e]];
+    po.st[e] = st[ax[e]];
+  }
+  po.nr = d3 ? po.n[1] : (po.n[1] + S.NR - 1) / S.NR * S.NR;
+  po.n_part = (po.n[0] + kC2 - 1) / kC2 * kC2 * po.n[2] * po.nr;
+  return po;
+}
+
 // (Re)build everything that depends on the plan: schedules, group tables and
 // the plan-dependent arrays.
-bte_status build_plan_impl(bte_ctx* h, const Plan& pl_in) {
+bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
   Plan pl = pl_in;
   const bool L3 = h->dim == 3;
   // 3D: NR >= 1 asks for the rows-per-lane layout, NR = 0 for the pencil blocks
@@ -413,6 +445,15 @@ bte_status build_plan_impl(bte_ctx* h, const Plan& pl_in) {
   std::vector<double> gtf, gta;
   int W_max = 1, e_max = 1, o_max = 1;
   int grp_tot = 0;
+  // accumulator planes: the temperature, and the heat flux or dJ/dQ.
+  // Second-order sweeps carry three planes on flux iterations in 1D too (the
+  // y-flux plane then holds zeros): one compiled variant per shape
+  h->nacc_max = std::max(1 + h->dim, h->order == 2 ? 3 : 2);
+  const bool rows = !L3 || R3;
+  h->part_extra = h->store_extra = 0;
+  auto al256 = [](size_t x) { return (long long)((x + kWsAlign - 1) / kWsAlign * kWsAlign); };
+  std::vector<int2> fb;   // finalize blocks
+  std::vector<int> nbi;
   for (size_t k = 0; k < h->inst.size(); ++k) {
     Inst& I = h->inst[k];
     std::string err;
@@ -463,10 +504,33 @@ bte_status build_plan_impl(bte_ctx* h, const Plan& pl_in) {
       gia.push_back(make_int4(gs.band[g], gs.oct[g] ^ (n_oct - 1), g, row));
     }
     // device arrays of the schedule
+    I.n_part = I.hi.ncell;
+    I.d_cell_of = nullptr;
+    int row_step = L3 ? 0 : I.hi.n[0];
+    if (L3) row_step = std::vector<int>{1, I.hi.n[0], I.hi.n[0] * I.hi.n[1]}[S.ax[1]];
     HIPCHK(pp.upload(&I.d_sched, S.sched));
-    HIPCHK(pp.upload(&I.d_pos, S.pos));
-    HIPCHK(pp.upload(&I.d_in_slot, S.in_slot));
-    HIPCHK(pp.upload(&I.d_in_chunk, S.in_chunk));
+    PlaneOrder po;
+    if (rows) po = plane_order(I.hi, S);
+    const bool blocks = rows && h->part_blocks && po.n_part < (1 << 26);  // (a record holds the index << 5)
+    if (blocks) {
+      I.n_part = po.n_part;
+      row_step = kC2;
+      // (the tables in this order are made on the device, below)
+      HIPCHK(pp.alloc(&I.d_pos, (size_t)S.n_oct * I.n_part));
+      HIPCHK(pp.alloc(&I.d_cell_of, I.n_part));
+      h->part_extra += al256((size_t)S.n_oct * I.n_part * 4) - al256(S.pos.size() * 4) + al256((size_t)I.n_part * 4);
+    } else {
+      HIPCHK(pp.upload(&I.d_pos, S.pos));
+    }
+    if (!rows) {
+      HIPCHK(pp.upload(&I.d_in_slot, S.in_slot));
+      HIPCHK(pp.upload(&I.d_in_chunk, S.in_chunk));
+    }
+    I.n_fblocks = (I.n_part + kFinCells - 1) / kFinCells;
+    HIPCHK(pp.alloc(&I.d_blockpart, (size_t)I.n_fblocks * 4));
+    for (int b = 0; b < I.n_fblocks; ++b) fb.push_back(make_int2((int)k, b));
+    nbi.push_back(I.n_fblocks);
+    h->fin_f[k].blockpart = h->fin_a[k].blockpart = I.d_blockpart;
     HIPCHK(pp.upload(&I.d_in_tab, S.in_tab));
     HIPCHK(pp.upload(&I.d_chunk_fl, S.chunk_fl));
     HIPCHK(pp.upload(&I.d_out_base, S.out_base));
@@ -517,7 +581,7 @@ bte_status build_plan_impl(bte_ctx* h, const Plan& pl_in) {
     HIPCHK(pp.alloc(&ov, (size_t)n_grp_inst * S.n_out_stride * es));
     I.d_outv = ov;
     char* pt;
-    I.part_ld = (I.hi.ncell + kPartBlk - 1) / kPartBlk * kPartBlk;
+    I.part_ld = (I.n_part + kPartBlk - 1) / kPartBlk * kPartBlk;
     // job groups: 1D/2D planes, and 3D ones up to 256 MiB, keep one job per
     // group (each job's cells contiguous); larger 3D ones group as many jobs
     // as keep a group's part of a plane within the 32-bit offsets of a buffer
@@ -526,8 +590,20 @@ bte_status build_plan_impl(bte_ctx* h, const Plan& pl_in) {
     I.part_jg = 0;
     if (h->dim == 3 && (size_t)I.part_ld * n_bund * es > (256ull << 20))
       while ((1 << I.part_jg) < n_bund && ((size_t)I.part_ld << (I.part_jg + 1)) * es < (1ull << 31)) ++I.part_jg;
-    HIPCHK(pp.alloc(&pt, (size_t)kNAcc * part_plane_len(n_bund, I.part_jg, I.part_ld) * es));
+    HIPCHK(pp.alloc(&pt, (size_t)h->nacc_max * part_plane_len(n_bund, I.part_jg, I.part_ld) * es));
     I.d_part = pt;
+    if (blocks && pp.mode != DevPool::COUNT) {
+      // the grid-order positions wait in the planes, which every octant has a
+      // job in; the null stream orders the kernel before the copies that follow
+      HIPCHK(hipMemcpy(I.d_part, S.pos.data(), S.pos.size() * 4, hipMemcpyHostToDevice));
+      HIPCHK(launch_plane_tables(po, I.hi.ncell, S.n_oct, reinterpret_cast<const int*>(I.d_part), I.d_pos, I.d_cell_of,
+                                 I.d_sched, (long long)S.sched.size(), nullptr));
+    }
+    const int ld0 = (I.hi.ncell + kPartBlk - 1) / kPartBlk * kPartBlk;
+    h->part_extra += al256((size_t)h->nacc_max * part_plane_len(n_bund, I.part_jg, I.part_ld) * es) -
+                     al256((size_t)h->nacc_max * part_plane_len(n_bund, I.part_jg, ld0) * es);
+    h->store_extra += al256((size_t)n_grp_inst * I.n_part * pl.G * es) -
+                      al256((size_t)n_grp_inst * I.hi.ncell * pl.G * es);
     I.d_store = nullptr;
     I.stored = false;
     I.have_dJds = false;
@@ -575,6 +651,8 @@ bte_status build_plan_impl(bte_ctx* h, const Plan& pl_in) {
       d.ubf = adj ? I.d_ubf0 : I.d_ubf;
       d.outv = I.d_outv;
       d.part = I.d_part;
+      d.n_part = I.n_part;
+      d.cell_of = I.d_cell_of;
       d.part_ld = I.part_ld;
       d.part_jg = I.part_jg;
       d.store_u = (!adj && h->order == 2) ? I.d_store : nullptr;
@@ -592,10 +670,9 @@ bte_status build_plan_impl(bte_ctx* h, const Plan& pl_in) {
       d.chunk_fl = I.d_chunk_fl;
       for (int e = 0; e < 3; ++e) d.ax[e] = S.ax[e];
       for (int oo = 0; oo < 8; ++oo) {
-        const int st[3] = {1, I.hi.n[0], I.hi.n[0] * I.hi.n[1]};
         // the groups of the transposed sweeps run the flipped octant's schedule,
         // and the kernel indexes with its job's (schedule) octant
-        d.dyo[oo] = ((oo >> S.ax[1]) & 1 ? -1 : 1) * st[S.ax[1]];
+        d.dyo[oo] = ((oo >> (L3 ? S.ax[1] : 1)) & 1 ? -1 : 1) * row_step;
       }
       d.n_pl = S.n_pl;
       d.n_per = S.n_per;
@@ -616,6 +693,13 @@ bte_status build_plan_impl(bte_ctx* h, const Plan& pl_in) {
   std::stable_sort(jf.begin(), jf.end(), [&](const JobDev& a, const JobDev& b) { return work(a) > work(b); });
   std::stable_sort(ja.begin(), ja.end(), [&](const JobDev& a, const JobDev& b) { return work(a) > work(b); });
   h->n_jobs = (int)jf.size();
+  h->n_fblocks = (int)fb.size();
+  HIPCHK(pp.upload(&h->d_fblocks, fb));
+  HIPCHK(pp.upload(&h->d_nblocks, nbi));
+  if (pp.mode != DevPool::COUNT) {
+    HIPCHK(hipMemcpy(h->d_fin_f, h->fin_f.data(), h->fin_f.size() * sizeof(FinInst), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(h->d_fin_a, h->fin_a.data(), h->fin_a.size() * sizeof(FinInst), hipMemcpyHostToDevice));
+  }
   HIPCHK(pp.upload(&h->d_inst_f, idf));
   HIPCHK(pp.upload(&h->d_inst_a, ida));
   HIPCHK(pp.upload(&h->d_jobs_f, jf));
@@ -633,9 +717,6 @@ bte_status build_plan_impl(bte_ctx* h, const Plan& pl_in) {
   }
   // LDS carve-up
   const int R = L3 ? 1 : pl.R, P = pl.P, G = pl.G, Cc = pl.C;
-  // second-order sweeps carry three planes on flux iterations in 1D too (the
-  // y-flux plane then holds zeros): one compiled variant per shape
-  h->nacc_max = std::max(1 + h->dim, h->order == 2 ? 3 : 2);
   auto al = [](size_t x) { return (x + 15) / 16 * 16; };
   size_t off = 0;
   SweepArgs& sa = h->sa;
@@ -771,16 +852,42 @@ bte_status finish_plan(bte_ctx* h, const Plan& pl, DevPool& pp) {
   const size_t es = elem(h->precision);
   size_t st = 0;
   for (auto& I : h->inst)
-    st += ((size_t)I.n_grp * I.hi.ncell * pl.G * es + kWsAlign - 1) / kWsAlign * kWsAlign;
+    st += ((size_t)I.n_grp * I.n_part * pl.G * es + kWsAlign - 1) / kWsAlign * kWsAlign;
   h->need_store = st;
   if (h->pool_mode == DevPool::ARENA && h->ws_store && h->order == 1) {
     for (auto& I : h->inst) {
       char* p;
-      HIPCHK(pp.alloc(&p, (size_t)I.n_grp * I.hi.ncell * pl.G * es));
+      HIPCHK(pp.alloc(&p, (size_t)I.n_grp * I.n_part * pl.G * es));
       I.d_store = p;
     }
   }
   return BTE_OK;
+}
+
+// Device workspace of bte_solve_noalloc (below): the largest need it accepts.
+constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
+
+// The plan's arrays with the partial-sum planes in blocks of columns, or in
+// grid order where the blocks' padding alone would push the need past the
+// allocation-free solve's fixed array (with or without the angular field).
+bte_status build_plan_impl(bte_ctx* h, const Plan& pl) {
+  // (the choice made while a plan was only counted holds when it is built:
+  // a bound workspace was sized for it)
+  const bool known = h->part_order == h->order && h->part_plan.G == pl.G && h->part_plan.R == pl.R &&
+                     h->part_plan.P == pl.P && h->part_plan.C == pl.C && h->part_plan.NR == pl.NR;
+  if (!known) h->part_blocks = true;
+  bte_status s = build_plan_arrays(h, pl);
+  if (s != BTE_OK || known) return s;
+  const long long lim = (long long)kStaticScratchBytes, need = (long long)(h->need_static + h->need_plan);
+  const long long with = need + (long long)h->need_store;
+  if ((need > lim && need - h->part_extra <= lim) ||
+      (with > lim && with - h->part_extra - h->store_extra <= lim)) {
+    h->part_blocks = false;
+    s = build_plan_arrays(h, pl);
+  }
+  h->part_plan = h->plan;
+  h->part_order = s == BTE_OK ? h->order : 0;
+  return s;
 }
 
 // (Re)build the plan-dependent state. With a bound workspace the plan's bytes
@@ -798,6 +905,7 @@ bte_status build_plan(bte_ctx* h, const Plan& pl) {
       return BTE_ERR_WORKSPACE;
     }
     HIPCHK(hipDeviceSynchronize());  // kernels in flight may still read the current plan's arrays
+    return build_plan_impl(h, Plan(h->plan));
   }
   return build_plan_impl(h, pl);
 }
@@ -818,8 +926,6 @@ bte_status build_static(bte_ctx* h) {
   HIPCHK(pp.memset(h->d_st_a, 0, n * sizeof(StatusDev)));
   HIPCHK(pp.alloc(&h->d_counters, 4));
   HIPCHK(pp.memset(h->d_counters, 0, 16));
-  std::vector<int2> fb;
-  std::vector<int> nbi;
   h->fin_f.resize(n);
   h->fin_a.resize(n);
   // specular walls (Eq. 7): the inflow of an ordinate is its mirror's outflow,
@@ -876,10 +982,6 @@ bte_status build_static(bte_ctx* h) {
     HIPCHK(pp.alloc(&I.d_qmag, hi.ncell));
     HIPCHK(pp.alloc(&I.d_qbuf, (size_t)hi.ncell * hi.dim));
     HIPCHK(pp.alloc(&I.d_dqbuf, hi.ncell));
-    I.n_fblocks = (hi.ncell + kFinCells - 1) / kFinCells;
-    HIPCHK(pp.alloc(&I.d_blockpart, (size_t)I.n_fblocks * 4));
-    for (int b = 0; b < I.n_fblocks; ++b) fb.push_back(make_int2(k, b));
-    nbi.push_back(I.n_fblocks);
     HIPCHK(pp.upload(&I.d_bf_bc, hi.bf_bc));
     HIPCHK(pp.upload(&I.d_bf_cell, hi.bf_cell));
     HIPCHK(pp.upload(&I.d_bc_kind, hi.bc_kind));
@@ -916,7 +1018,6 @@ bte_status build_static(bte_ctx* h) {
     ff.g = nullptr;
     ff.q = I.d_qbuf;
     ff.qmag_prev = I.d_qmag;
-    ff.blockpart = I.d_blockpart;
     ff.active = I.d_active;
     FinInst& fa = h->fin_a[k];
     fa = ff;
@@ -924,11 +1025,8 @@ bte_status build_static(bte_ctx* h) {
     fa.X[1] = I.d_Xa[1];
     fa.q = I.d_dqbuf;
   }
-  h->n_fblocks = (int)fb.size();
-  HIPCHK(pp.upload(&h->d_fblocks, fb));
-  HIPCHK(pp.upload(&h->d_nblocks, nbi));
-  HIPCHK(pp.upload(&h->d_fin_f, h->fin_f));
-  HIPCHK(pp.upload(&h->d_fin_a, h->fin_a));
+  HIPCHK(pp.alloc(&h->d_fin_f, n));  // filled with the plan's arrays
+  HIPCHK(pp.alloc(&h->d_fin_a, n));
   h->need_static = pp.used;
   for (auto& I : h->inst) {
     I.stored = false;
@@ -1307,7 +1405,7 @@ bte_status init_forward(bte_ctx* h, size_t k, const double* d_Q, const double* d
   a.X[0] = I.d_X[0];
   a.X[1] = I.d_X[1];
   a.adjoint = 0;
-  HIPCHK(launch_init_state(h->precision, a, I.hi.ncell, st));
+  HIPCHK(launch_init_state(h->precision, a, I.n_part, st));
   HIPCHK(launch_zero(I.d_qmag, (size_t)I.hi.ncell * 8, st));
   UbfInitArgs u;
   u.ubf = I.d_ubf;
@@ -1358,7 +1456,7 @@ bte_status store_state(bte_ctx* h, hipStream_t st) {
         return BTE_ERR_WORKSPACE;
       }
       char* p;
-      HIPCHK(h->ppool->alloc(&p, (size_t)I.n_grp * I.hi.ncell * h->plan.G * es));
+      HIPCHK(h->ppool->alloc(&p, (size_t)I.n_grp * I.n_part * h->plan.G * es));
       I.d_store = p;
     }
     idf[k].store_u = I.d_store;
@@ -1574,7 +1672,6 @@ bte_status solve_impl(bte_ctx* h, const double* h_tau, const double* d_Q, const 
 // held until the process ends). Host code never uses the array's name as an
 // address: the device address comes from hipGetSymbolAddress, once per
 // device, and is kept per device.
-constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -2008,7 +2105,7 @@ static bte_status adjoint_common(bte_handle h, const double* const* d_dJdT, doub
     a.X[0] = I.d_Xa[0];
     a.X[1] = I.d_Xa[1];
     a.adjoint = 1;
-    HIPCHK(launch_init_state(h->precision, a, I.hi.ncell, st));
+    HIPCHK(launch_init_state(h->precision, a, I.n_part, st));
     HIPCHK(launch_status_reset(h->d_st_a + k, (double)I.hi.n_active, st));
     HIPCHK(launch_zero(I.d_tgrad, (size_t)I.n_grp * 2 * 8, st));
   }

@@ -54,14 +54,14 @@ __device__ __forceinline__ void job_sum_vec(const T* pl, int n_jobs, int jg, int
 // in LDS, and thread cl < kFinCells returns cell cl's total (pairwise over the
 // slices in a fixed order); the others return 0.
 template <typename T>
-__device__ __forceinline__ double plane_total(const T* pl, int n_jobs, int jg, int part_ld, int ncell, int cbase,
+__device__ __forceinline__ double plane_total(const T* pl, int n_jobs, int jg, int part_ld, int n_part, int cbase,
                                               double (*slc)[kFinCells]) {
   using Sh = FinShape<T>;
   const int t = threadIdx.x;
   const int gi = t % Sh::NG, js = t / Sh::NG;
   const int c0 = cbase + gi * Sh::VW;
   double acc[Sh::VW];
-  if (c0 < ncell) {
+  if (c0 < n_part) {
     job_sum_vec(pl + ((size_t)cbase << jg), n_jobs, jg, part_ld, gi * Sh::VW, js, acc);
   } else {
 #pragma unroll
@@ -126,9 +126,10 @@ __global__ void __launch_bounds__(kFinThreads) finalize_kernel(FinArgs A, const 
   __syncthreads();
   const int iter = s_iter;
   const int cur = iter & 1, nxt = cur ^ 1;
-  const int cl = threadIdx.x;  // the cell of threads < kFinCells
+  const int cl = threadIdx.x;  // the plane index (and its cell) of threads < kFinCells
   const int cbase = bi.y * kFinCells;
-  const int c = cbase + cl;
+  const int pc = cbase + cl;
+  const int c = cl < kFinCells && pc < I.n_part ? (I.cell_of ? I.cell_of[pc] : pc) : -1;
   const size_t plane = (size_t)part_plane_len(I.n_jobs, I.part_jg, I.part_ld);
   const T* part = reinterpret_cast<const T*>(I.part);
   const bool adj = (A.flags & FIN_ADJ) != 0, withq = (A.flags & FIN_Q) != 0;
@@ -136,10 +137,10 @@ __global__ void __launch_bounds__(kFinThreads) finalize_kernel(FinArgs A, const 
   // ---- per-cell totals of every needed plane (inactive cells' entries are
   //      gathered with their neighbours and dropped below)
   double tot[4];
-  tot[0] = plane_total(part, I.n_jobs, I.part_jg, I.part_ld, I.ncell, cbase, slc);
+  tot[0] = plane_total(part, I.n_jobs, I.part_jg, I.part_ld, I.n_part, cbase, slc);
   for (int d = 0; d < nq; ++d)
-    tot[1 + d] = plane_total(part + (size_t)(1 + d) * plane, I.n_jobs, I.part_jg, I.part_ld, I.ncell, cbase, slc);
-  const bool in_blk = cl < kFinCells && c < I.ncell;
+    tot[1 + d] = plane_total(part + (size_t)(1 + d) * plane, I.n_jobs, I.part_jg, I.part_ld, I.n_part, cbase, slc);
+  const bool in_blk = c >= 0;
   const bool act = in_blk && F.active[c];
   double v[4] = {0.0, 0.0, 0.0, 0.0};  // sum dT^2, max |x|, sum d|q|^2, max |q| (+inf: non-finite)
   if (in_blk) {
@@ -151,7 +152,7 @@ __global__ void __launch_bounds__(kFinThreads) finalize_kernel(FinArgs A, const 
       // scatter into the skewed layouts of every octant
       T* xq = reinterpret_cast<T*>(I.xq[nxt]);
       for (int o = 0; o < I.n_oct; ++o) {
-        const int ps = I.pos[(size_t)o * I.ncell + c];
+        const int ps = I.pos[(size_t)o * I.n_part + pc];
         xq[2 * ((size_t)o * I.pos_per_oct + ps)] = (T)x;
       }
       bool bad = !isfinite(x);
@@ -329,8 +330,10 @@ __global__ void __launch_bounds__(256) spec_update_kernel(SpecArgs A) {
 template <typename T>
 __global__ void __launch_bounds__(256) init_state_kernel(InitArgs A) {
   const InstDev& I = A.inst[A.inst_id];
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= I.ncell) return;
+  const int pc = blockIdx.x * 256 + threadIdx.x;  // plane index
+  if (pc >= I.n_part) return;
+  const int c = I.cell_of ? I.cell_of[pc] : pc;
+  if (c < 0) return;
   double x = 0.0, q = 0.0;
   if (A.active[c]) {
     if (A.X0) x = A.adjoint ? A.X0[c] : (A.X0[c] - A.T_ref);
@@ -342,7 +345,7 @@ __global__ void __launch_bounds__(256) init_state_kernel(InitArgs A) {
   for (int b = 0; b < 2; ++b) {
     T* xq = reinterpret_cast<T*>(I.xq[b]);
     for (int o = 0; o < I.n_oct; ++o) {
-      const int ps = I.pos[(size_t)o * I.ncell + c];
+      const int ps = I.pos[(size_t)o * I.n_part + pc];
       xq[2 * ((size_t)o * I.pos_per_oct + ps)] = (T)x;
       xq[2 * ((size_t)o * I.pos_per_oct + ps) + 1] = (T)q;
     }
@@ -557,11 +560,36 @@ __global__ void __launch_bounds__(256) corr_fill_kernel(CorrArgs A) {
       o = og;
       const int2 rec = I.sched[(size_t)o * (I.pos_per_oct / nr) + p / nr];
       const bool on = rec.x >= 0 && ((rec.y >> (rb * k)) & 1);
-      const int dy = I.dim == 3 ? I.dyo[o] : ((o & 2) ? -I.nx : I.nx);
-      v = on ? (T)A.X0[(rec.x >> 5) + k * dy] : T(0);
+      const int i = (rec.x >> 5) + k * I.dyo[o];
+      v = on ? (T)A.X0[I.cell_of ? I.cell_of[i] : i] : T(0);
     }
     reinterpret_cast<T*>(I.store_u)[(size_t)g * I.pos_per_oct + p] = v;
   }
+}
+
+// The tables of a blocked plane order: the cell of each plane index (-1:
+// padding), the octants' positions by plane index (pos_c: by cell), and the
+// plane index of each record's first row in place of its cell.
+__global__ void __launch_bounds__(256) plane_index_kernel(PlaneOrder po, int ncell, int n_oct, const int* pos_c, int* pos,
+                                                          int* cell_of) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= po.n_part) return;
+  int t = i / kC2;
+  const int row = t % po.nr;
+  t /= po.nr;
+  const int pl = t % po.n[2], col = t / po.n[2] * kC2 + i % kC2;
+  const int c = col < po.n[0] && row < po.n[1] ? col * po.st[0] + row * po.st[1] + pl * po.st[2] : -1;
+  cell_of[i] = c;
+  for (int o = 0; o < n_oct; ++o) pos[(size_t)o * po.n_part + i] = c >= 0 ? pos_c[(size_t)o * ncell + c] : -1;
+}
+__global__ void __launch_bounds__(256) plane_record_kernel(PlaneOrder po, int2* sched, long long n_sched) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n_sched) return;
+  const int v = sched[i].x;
+  if (v < 0) return;
+  const int c = v >> 5;
+  const int col = c / po.st[0] % po.n[0], row = c / po.st[1] % po.n[1], pl = c / po.st[2] % po.n[2];
+  sched[i].x = (((col / kC2 * po.n[2] + pl) * po.nr + row) * kC2 + col % kC2) << 5 | (v & 31);
 }
 
 template __global__ void finalize_kernel<float>(FinArgs, const FinInst*);
@@ -602,11 +630,18 @@ hipError_t launch_wall_update(int prec, const WallArgs& a, int n_oct, hipStream_
   return hipGetLastError();
 }
 
-hipError_t launch_init_state(int prec, const InitArgs& a, int ncell, hipStream_t st) {
+hipError_t launch_plane_tables(const PlaneOrder& po, int ncell, int n_oct, const int* pos_c, int* pos, int* cell_of,
+                               int2* sched, long long n_sched, hipStream_t st) {
+  hipLaunchKernelGGL(plane_index_kernel, dim3(nblk(po.n_part)), dim3(256), 0, st, po, ncell, n_oct, pos_c, pos, cell_of);
+  hipLaunchKernelGGL(plane_record_kernel, dim3(nblk(n_sched)), dim3(256), 0, st, po, sched, n_sched);
+  return hipGetLastError();
+}
+
+hipError_t launch_init_state(int prec, const InitArgs& a, int n_part, hipStream_t st) {
   if (prec == BTE_PREC_FP32)
-    hipLaunchKernelGGL(init_state_kernel<float>, dim3(nblk(ncell)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(init_state_kernel<float>, dim3(nblk(n_part)), dim3(256), 0, st, a);
   else
-    hipLaunchKernelGGL(init_state_kernel<double>, dim3(nblk(ncell)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(init_state_kernel<double>, dim3(nblk(n_part)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -119,7 +119,8 @@ struct InstDev {
                           //   R*(T + kPad2)*64 (3D pencil blocks)
   // schedule (per octant, R slots): cell index (-1 idle/inactive) and flags
   const int2* sched;        // [n_oct][R][T + kPad2][64] (cell, flags)
-  const int* pos;           // [n_oct][ncell] position of cell c in octant o's layout (-1 inactive)
+  const int* pos;           // [n_oct][n_part] position of the cell at plane index i in octant o's layout
+                            //   (-1: inactive or none)
   // inflow stream: boundary-face slots in consumption order, per (octant, slot)
   const int* in_slot;       // concatenated
   const int* in_chunk;      // [n_oct][R][nchunks+1] start offset of each chunk (absolute into in_slot)
@@ -133,9 +134,17 @@ struct InstDev {
   void* part;               // [kNAcc] planes of partial sums (sweep precision), each in groups of
                             //   2^part_jg jobs, cell-block major inside a group:
                             //   [n_jobs / 2^part_jg][part_ld / kPartBlk][2^part_jg][kPartBlk]
-  int part_ld;              // cells per job in a plane: ncell rounded up to a multiple of kPartBlk
+  // order of the cells in a partial-sum plane (and in the angular field kept
+  // for the adjoint): the rows-per-lane layouts take blocks of kC2 columns of
+  // the step axis, in a block plane after plane, row after row, the kC2
+  // columns of a row side by side; cell_of maps a plane index to its cell
+  // (-1: padding), NULL: the cell index itself. The sched records hold the
+  // plane index of the lane's first row, dyo the index step to the next row.
+  int n_part;               // indices of a plane
+  const int* cell_of;       // [n_part]
+  int part_ld;              // cells per job in a plane: n_part rounded up to a multiple of kPartBlk
   int part_jg;              // log2 of the jobs per group (a group's part of a plane < 2 GiB)
-  void* store_u;            // [n_grp][ncell][G] angular field u (forward, when stored for the
+  void* store_u;            // [n_grp][n_part][G] angular field u (forward, when stored for the
                             //   adjoint); second-order faces: [n_grp][pos_per_oct] in the octant's
                             //   skewed layout
   double* tgrad;            // [n_grp][2] tau-gradient partial sums
@@ -155,7 +164,7 @@ struct InstDev {
   void* corr;               // [n_grp][pos_per_oct] sweep precision
   // 3D rows-per-lane layout
   int ax[3];                // grid axis of the step, lane and plane axes
-  int dyo[8];               // cell-index step from row k to row k + 1, per octant
+  int dyo[8];               // (1D/2D too) plane-index step from row k to row k + 1, per octant
   int n_pl;                 // planes
   int n_per;                // plane periods of kC2 steps (the most of any octant)
   const int* xpre;          // [n_oct][n_pl][64*nr] step-axis wall face of the first column's cells (-1)
@@ -320,6 +329,15 @@ struct CorrArgs {
                              //   first sweep), or NULL: the field the last sweep stored
 };
 constexpr int kNoCell = (int)0x80000000;  // stencil code of a position of no cell
+
+// Blocked order of the cells in a partial-sum plane: kernel axes (step, lane,
+// plane), their cell counts and cell-index strides; nr: rows, padded.
+struct PlaneOrder {
+  int n[3] = {1, 1, 1};
+  int st[3] = {0, 0, 0};
+  int nr = 1;
+  int n_part = 0;
+};
 
 struct InitArgs {
   const InstDev* inst;

@@ -33,7 +33,9 @@ int sweep3r_blocks_per_cu(int prec, int NR, int P, int nacc, int mode, int block
 hipError_t launch_finalize(int prec, const FinArgs& a, const FinInst* fi, hipStream_t st);
 hipError_t launch_wall_update(int prec, const WallArgs& a, int n_oct, hipStream_t st);
 hipError_t launch_spec_update(int prec, const SpecArgs& a, hipStream_t st);
-hipError_t launch_init_state(int prec, const InitArgs& a, int ncell, hipStream_t st);
+hipError_t launch_plane_tables(const PlaneOrder& po, int ncell, int n_oct, const int* pos_c, int* pos, int* cell_of,
+                               int2* sched, long long n_sched, hipStream_t st);
+hipError_t launch_init_state(int prec, const InitArgs& a, int n_part, hipStream_t st);
 hipError_t launch_output(const double* X, const unsigned char* active, int n, double T_ref,
                          double add_ref, double* out, hipStream_t st);
 hipError_t launch_status_reset(StatusDev* stt, double n_active, hipStream_t st);

@@ -253,7 +253,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
     const int du = I.du, n_strip = I.n_strip;
     const bool ring_w = !L3 && n_strip > 1;  // some strip has a successor (1D/2D lane-axis link)
     const int H = 64 * NR;
-    const int dy = L3 ? I.dyo[o] : ((o & 2) ? -nx : nx);  // cell-index step from row k to row k+1
+    const int dy = I.dyo[o];  // plane-index step from row k to row k+1
     const long long slot = (long long)o * R + r;
     // uniform bases; lanes add 32-bit offsets
     const GAS int2* REC = gp(I.sched + slot * Tp * 64);
@@ -565,16 +565,16 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
             for (int q = 1; q < PQ; ++q) sm += wraw[PS ? 0 : a][mi][q];
           }
           if constexpr (!L3) {
-            // 1D/2D planes keep one job per group: the cell index itself. The
-            // lane axis is the grid's slowest, so a row of the lane outside
-            // the grid has a cell index past either end of the plane (or in
-            // the job's padding) and the buffer's range check drops it
+            // 1D/2D planes keep one job per group: the plane index itself. A
+            // row of the lane outside the grid lands in the planes' padding
+            // rows, or past either end of the plane, where the buffer's range
+            // check drops it
 #pragma unroll
             for (int k = 0; k < NR; ++k) bst(sm[k], PRS[a], v >= 0 ? (cid0 + k * dy) * (int)sizeof(T) : kOOB);
           } else {
-            // 3D: the lane axis may be a faster grid axis, where the index of
-            // a row past the grid's end is a cell of the next line: rows
-            // outside the grid (record bit k clear) are not stored
+            // 3D: planes have no padding rows, the index of a row past the
+            // grid's end is a cell of the next line: rows outside the grid
+            // (record bit k clear) are not stored
 #pragma unroll
             for (int k = 0; k < NR; ++k) {
               const int c = cid0 + k * dy;
@@ -891,7 +891,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
           for (int k = 0; k < NR; ++k)
             if ((fl >> (RB * k)) & B_ACT) {
               GAS T* su =
-                  gp(reinterpret_cast<T*>(I.store_u) + ((size_t)g_loc * I.ncell + (rec.x >> 5) + k * dy) * G);
+                  gp(reinterpret_cast<T*>(I.store_u) + ((size_t)g_loc * I.n_part + (rec.x >> 5) + k * dy) * G);
 #pragma unroll
               for (int g = 0; g < G; ++g) su[g] = f[g][k] * inv[g];
             }
@@ -903,7 +903,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
           for (int k = 0; k < NR; ++k)
             if ((fl >> (RB * k)) & B_ACT) {
               const GAS T* su =
-                  gp(reinterpret_cast<const T*>(I.store_u) + ((size_t)g_loc * I.ncell + (rec.x >> 5) + k * dy) * G);
+                  gp(reinterpret_cast<const T*>(I.store_u) + ((size_t)g_loc * I.n_part + (rec.x >> 5) + k * dy) * G);
               double s0 = 0.0, s1 = 0.0;
 #pragma unroll
               for (int g = 0; g < G; ++g) {
