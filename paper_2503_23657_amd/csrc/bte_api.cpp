@@ -157,7 +157,13 @@ struct Inst {
   double* d_tgrad = nullptr;
   void* d_corr = nullptr;         // second-order faces: [n_grp][pos_per_oct] correction
   double* d_corr_coef = nullptr;  // [n_grp][3]
-  int* d_stencil = nullptr;       // [n_oct][pos_per_oct][3*dim] Green-Gauss stencil codes
+  int* d_stencil = nullptr;       // [n_oct][pos_per_oct][3*dim] Green-Gauss stencil codes (gather kernel)
+  unsigned* d_ccode = nullptr;    // marching kernel: boundary codes, isothermal walls, units, block links
+  int* d_cwslot = nullptr;
+  int2* d_cunit = nullptr;
+  int2* d_clink = nullptr;
+  CorrTables ctab;                // host tables of the marching kernel, and whether they hold for the schedule
+  bool ctab_made = false, ctab_ok = false;
   int* d_xpre = nullptr;          // 3D rows-per-lane: step-axis wall faces of the first column
   int* d_gpre = nullptr;          // 3D rows-per-lane: lane 0's lane-axis wall faces
   int* d_out_tab = nullptr;       // 3D rows-per-lane: outflow entries per chunk
@@ -462,6 +468,7 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
       return BTE_ERR_INVALID;
     }
     const Schedule& S = I.sch;
+    if (!reuse_sched) I.ctab_made = false;
     if (h->has_specular) {
       // every mirror ordinate must find its outflow entry at each specular face
       const int nbf = (int)I.hi.bf_cell.size();
@@ -619,7 +626,21 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
       HIPCHK(pp.alloc(&ps, nc));
       I.d_store = ps;
       HIPCHK(pp.upload(&I.d_corr_coef, corr_coefficients(h, I.hi)));
-      HIPCHK(pp.upload(&I.d_stencil, corr_stencil(I.hi, S)));
+      // one strip: the marching kernel's tables; else (or should a neighbour
+      // not sit where that kernel looks for it) the gather kernel's stencil
+      const CorrTables& ct = I.ctab;
+      if (!I.ctab_made) I.ctab_ok = corr_tables(I.hi, S, n_grp_inst, I.ctab);
+      I.ctab_made = true;
+      I.d_stencil = nullptr;
+      I.d_ccode = nullptr;
+      if (I.ctab_ok) {
+        HIPCHK(pp.upload(&I.d_ccode, ct.code));
+        HIPCHK(pp.upload(&I.d_cwslot, ct.wslot));
+        HIPCHK(pp.upload(&I.d_cunit, ct.unit));
+        HIPCHK(pp.upload(&I.d_clink, ct.link));
+      } else {
+        HIPCHK(pp.upload(&I.d_stencil, corr_stencil(I.hi, S)));
+      }
     }
     // descriptors
     for (int adj = 0; adj < 2; ++adj) {
@@ -1248,20 +1269,34 @@ bte_status enqueue_specular(bte_ctx* h, bool adj, hipStream_t st) {
   return BTE_OK;
 }
 
+CorrArgs corr_args(const bte_ctx* h, size_t k) {
+  const Inst& I = h->inst[k];
+  CorrArgs a{};
+  a.inst = h->d_inst_f;
+  a.inst_id = (int)k;
+  a.n_grp = I.n_grp;
+  a.grp = h->d_gi_f + I.grp0;
+  a.coef = I.d_corr_coef;
+  a.stencil = I.d_stencil;
+  a.code = I.d_ccode;
+  a.wslot = I.d_cwslot;
+  a.n_slot = h->dim == 3 ? 1 : I.sch.R;
+  a.n_unit = I.ctab.n_unit;
+  a.seg = I.ctab.seg;
+  a.tail = I.ctab.tail;
+  a.unit = I.d_cunit;
+  a.link = I.d_clink;
+  for (int d = 0; d < 3; ++d) a.h[d] = I.hi.h[d];
+  a.X0 = nullptr;
+  return a;
+}
+
 // Second-order faces: the next sweep's correction from the stored field.
 bte_status enqueue_corr(bte_ctx* h, hipStream_t st) {
   for (size_t k = 0; k < h->inst.size(); ++k) {
     Inst& I = h->inst[k];
-    CorrArgs a;
-    a.inst = h->d_inst_f;
-    a.inst_id = (int)k;
-    a.n_grp = I.n_grp;
-    a.grp = h->d_gi_f + I.grp0;
-    a.coef = I.d_corr_coef;
-    a.stencil = I.d_stencil;
-    for (int d = 0; d < 3; ++d) a.h[d] = I.hi.h[d];
-    a.X0 = nullptr;
-    HIPCHK(launch_corr(h->precision, a, I.sch.pos_per_oct, st));
+    CorrArgs a = corr_args(h, k);
+    HIPCHK(launch_corr(h->precision, a, I.sch.pos_per_oct, I.sch.NR, h->dim == 3, st));
   }
   return BTE_OK;
 }
@@ -1425,16 +1460,9 @@ bte_status init_forward(bte_ctx* h, size_t k, const double* d_Q, const double* d
   if (h->order == 2) {
     // the first sweep's correction: the initial field is the equilibrium at
     // the initial temperature, the same for every ordinate
-    CorrArgs a;
-    a.inst = h->d_inst_f;
-    a.inst_id = (int)k;
-    a.n_grp = I.n_grp;
-    a.grp = h->d_gi_f + I.grp0;
-    a.coef = I.d_corr_coef;
-    a.stencil = I.d_stencil;
-    for (int d = 0; d < 3; ++d) a.h[d] = I.hi.h[d];
+    CorrArgs a = corr_args(h, k);
     a.X0 = I.d_X[0];
-    HIPCHK(launch_corr(h->precision, a, I.sch.pos_per_oct, st));
+    HIPCHK(launch_corr(h->precision, a, I.sch.pos_per_oct, I.sch.NR, h->dim == 3, st));
   }
   return BTE_OK;
 }

@@ -676,13 +676,14 @@ hipError_t launch_ubf_init(int prec, const UbfInitArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_corr(int prec, const CorrArgs& a, long long n_pos, hipStream_t st) {
+hipError_t launch_corr(int prec, const CorrArgs& a, long long n_pos, int nr, bool d3, hipStream_t st) {
   if (a.n_grp <= 0 || n_pos <= 0) return hipSuccess;
   const dim3 grid(nblk(n_pos), (a.n_grp + kCorrGrp - 1) / kCorrGrp);
   if (a.X0) {
     if (prec == BTE_PREC_FP32) hipLaunchKernelGGL(corr_fill_kernel<float>, grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL(corr_fill_kernel<double>, grid, dim3(256), 0, st, a);
   }
+  if (a.code) return launch_corr_march(prec, a, nr, d3, st);
   if (prec == BTE_PREC_FP32) hipLaunchKernelGGL(corr_kernel<float>, grid, dim3(256), 0, st, a);
   else hipLaunchKernelGGL(corr_kernel<double>, grid, dim3(256), 0, st, a);
   return hipGetLastError();

@@ -325,10 +325,31 @@ struct CorrArgs {
                              //   (downwind, upwind, upwind's upwind per axis; -1 boundary,
                              //   -(2 + slot) isothermal inflow wall, kNoCell first: no cell)
   double h[3];
+  // one-strip layouts: the marching kernel's tables (code NULL: the stencil
+  // and the gather kernel)
+  const unsigned* code;      // [n_oct][steps][64] CC_* bits, 4 per row k and kernel axis e at 4*(k*nd + e)
+                             //   (nd: 2 in 1D/2D, 3 in 3D)
+  const int* wslot;          // [n_oct][nd] boundary face whose value every isothermal upwind wall of the
+                             //   octant along the kernel axis has (-1: none)
+  int n_slot;                // wave slots of the layout (only the first holds cells)
+  int n_unit;                // units of a group, one wave each: 1D/2D seg chunks, 3D periods of one block
+  int seg;                   // 1D/2D: chunks of a unit
+  int tail;                  // 3D: chunks from a period's first lane to its last
+  const int2* unit;          // 3D: [n_oct][n_unit] first and past-the-end plane period of each unit (equal: none)
+  const int2* link;          // 3D: [n_oct][n_per] period of the previous / next block in the same plane, + 1
+                             //   (0: none)
   const double* X0;          // [ncell] equilibrium field of every ordinate, filled in first (before the
                              //   first sweep), or NULL: the field the last sweep stored
 };
 constexpr int kNoCell = (int)0x80000000;  // stencil code of a position of no cell
+// boundary code of a row along one kernel axis (0: every neighbour is a cell)
+constexpr unsigned CC_NODN = 1;    // no downwind cell
+constexpr unsigned CC_ISO = 2;     // the missing upwind side is an isothermal inflow wall
+constexpr unsigned CC_UP = 12;     // two bits:
+constexpr unsigned CC_NOUU = 4;    //   no cell twice upwind
+constexpr unsigned CC_NOUP = 8;    //   no upwind cell
+constexpr unsigned CC_NOCELL = 12; //   (axis 0) the row is no cell
+constexpr unsigned CC_IDLE = ~0u;  // (the whole word) no row of the lane is a cell: its correction stays 0
 
 // Blocked order of the cells in a partial-sum plane: kernel axes (step, lane,
 // plane), their cell counts and cell-index strides; nr: rows, padded.

@@ -93,7 +93,13 @@ __device__ __forceinline__ V ldv(rsrc_t r, int voff, int soff) {
 }
 
 // store of a vector of V at byte offsets voff (per lane) + soff (uniform); an
-// offset past the buffer drops the store
+// offset past the buffer drops the store. Stores of 16 bytes take the whole
+// offset per lane: with the uniform part in a scalar register the compiler
+// counts no hazard between the store and the next instruction's write of its
+// data registers, and such stores have written the new values here (the
+// marching correction kernel, a mask written to the first data register right
+// after the store: wrong values now and then); with no scalar offset it keeps
+// the wait state.
 template <typename V>
 __device__ __forceinline__ void stv(const V& v, rsrc_t r, int voff, int soff) {
   constexpr int B = (int)sizeof(V);
@@ -110,7 +116,7 @@ __device__ __forceinline__ void stv(const V& v, rsrc_t r, int voff, int soff) {
     };
     const Parts t = __builtin_bit_cast(Parts, v);
 #pragma unroll
-    for (int i = 0; i < B / 16; ++i) __builtin_amdgcn_raw_buffer_store_b128(t.q[i], r, voff + 16 * i, soff, 0);
+    for (int i = 0; i < B / 16; ++i) __builtin_amdgcn_raw_buffer_store_b128(t.q[i], r, voff + soff + 16 * i, 0, 0);
   }
 }
 

@@ -43,6 +43,8 @@ hipError_t launch_ubf_init(int prec, const UbfInitArgs& a, hipStream_t st);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
 // second-order faces: the correction of every group from the stored field,
 // and the stored field set to the initial temperature deviation X
-hipError_t launch_corr(int prec, const CorrArgs& a, long long n_pos, hipStream_t st);
+// (one-strip layouts: by the marching kernel, a.code set; others: by gathers)
+hipError_t launch_corr(int prec, const CorrArgs& a, long long n_pos, int nr, bool d3, hipStream_t st);
+hipError_t launch_corr_march(int prec, const CorrArgs& a, int nr, bool d3, hipStream_t st);
 
 }  // namespace bte

@@ -669,6 +669,7 @@ static bool build_3r_axes(const HostInst& hi, int A0, int A1, int A2, const Plan
         s.gpre[(size_t)o * (T + n_per) + T + q] = p + 1;
       }
   }
+  s.per_b = per_b;
   std::vector<int> out_face((size_t)NR * 3 * 64);
   std::vector<int> out_count(n_oct, 0);
   std::vector<std::vector<int>> out_ent(n_oct);
@@ -1048,6 +1049,140 @@ std::vector<int> corr_stencil(const HostInst& hi, const Schedule& s) {
     }
   }
   return out;
+}
+
+// Units: long enough that what a wave reads twice (1D/2D 3 steps, 3D 2 chunks
+// and the skew of its lanes) stays small, short enough that the groups of a
+// small problem still fill the chip's 1024 SIMDs several times.
+constexpr long long kCorrWaves = 4096;
+
+bool corr_tables(const HostInst& hi, const Schedule& s, int n_grp, CorrTables& out) {
+  out = CorrTables();
+  if (s.nS != 1 || (hi.dim == 3 && !s.l3r)) return false;
+  const bool d3 = hi.dim == 3;
+  const int nd = d3 ? 3 : 2, NR = s.NR, C = kC2;
+  const int ax[3] = {d3 ? s.ax[0] : 0, d3 ? s.ax[1] : 1, d3 ? s.ax[2] : 2};
+  const int st[3] = {1, hi.n[0], hi.n[0] * hi.n[1]};
+  const long long ppo = s.pos_per_oct;
+  const int R = d3 ? 1 : s.R, n_step = (int)(ppo / ((long long)64 * NR * R));
+  const int step = 64 * NR;  // positions of one step
+  if (d3) {
+    int nb = 0;
+    for (int b : s.per_b) nb = std::max(nb, b + 1);
+    out.tail = ((hi.n[ax[1]] + NR - 1) / NR + C - 1) / C;
+    // periods of a unit: a whole block, or at least twice the lanes' skew
+    const long long all = (long long)n_grp * s.n_per;
+    const int len = (int)std::max<long long>(all / kCorrWaves, 2 * out.tail);
+    std::vector<std::vector<int2>> units(s.n_oct);
+    out.link.assign((size_t)s.n_oct * s.n_per, make_int2(0, 0));
+    for (int o = 0; o < s.n_oct; ++o) {
+      const int* pb = &s.per_b[(size_t)o * s.n_per];
+      const int* pp = &s.gpre[(size_t)o * (s.T + s.n_per) + s.T];  // plane + 1
+      for (int q = 0; q < s.n_per;) {
+        int e = q;
+        while (e < s.n_per && pb[e] == pb[q]) ++e;
+        if (pb[q] >= 0)
+          for (int k = 0, n = std::max(1, (e - q) / len); k < n; ++k)
+            units[o].push_back(make_int2(q + (int)((long long)(e - q) * k / n), q + (int)((long long)(e - q) * (k + 1) / n)));
+        q = e;
+      }
+      std::vector<int> at((size_t)nb * (s.n_pl + 1), -1);
+      for (int q = 0; q < s.n_per; ++q) {
+        if (pb[q] < 0) continue;
+        at[(size_t)pb[q] * (s.n_pl + 1) + pp[q]] = q;
+      }
+      for (int q = 0; q < s.n_per; ++q) {
+        if (pb[q] < 0) continue;
+        int2& l = out.link[(size_t)o * s.n_per + q];
+        if (pb[q] > 0) l.x = at[(size_t)(pb[q] - 1) * (s.n_pl + 1) + pp[q]] + 1;
+        if (pb[q] + 1 < nb) l.y = at[(size_t)(pb[q] + 1) * (s.n_pl + 1) + pp[q]] + 1;
+      }
+    }
+    for (const auto& u : units) out.n_unit = std::max(out.n_unit, (int)u.size());
+    out.unit.assign((size_t)s.n_oct * out.n_unit, make_int2(0, 0));
+    for (int o = 0; o < s.n_oct; ++o) std::copy(units[o].begin(), units[o].end(), out.unit.begin() + (size_t)o * out.n_unit);
+  } else {
+    const int nch = n_step / C - 1;
+    out.seg = (int)std::min<long long>(8, std::max<long long>(1, (long long)n_grp * nch / kCorrWaves));
+    out.n_unit = (nch + out.seg - 1) / out.seg;
+  }
+  unsigned none = 0;  // rows of no cell beside one that is
+  for (int k = 0; k < NR; ++k) none |= CC_NOCELL << (4 * k * nd);
+  out.code.assign((size_t)s.n_oct * n_step * 64, CC_IDLE);
+  out.wslot.assign((size_t)s.n_oct * nd, -1);
+  for (int o = 0; o < s.n_oct; ++o) {
+    const int* pos = s.pos.data() + (size_t)o * hi.ncell;
+    unsigned* code = out.code.data() + (size_t)o * n_step * 64;
+    const int2* link = d3 ? out.link.data() + (size_t)o * s.n_per : nullptr;
+    for (int c = 0; c < hi.ncell; ++c) {
+      if (!hi.active[c] || pos[c] < 0) continue;
+      const int p = pos[c], k = p % NR, l = p / NR % 64, t = p / step;
+      if (t >= n_step) return false;
+      const int x[3] = {c % hi.n[0], (c / hi.n[0]) % hi.n[1], c / (hi.n[0] * hi.n[1])};
+      const int row = l * NR + k;
+      // positions of the cells `by` rows or columns or planes on (by < 0: upwind)
+      auto expect = [&](int e, int by) -> long long {
+        if (e == 1) {
+          const int r = row + by, dl = r / NR - l;
+          return r < 0 ? -1 : ((long long)(t + dl) * 64 + r / NR) * NR + r % NR;
+        }
+        if (e == 2) return p + (long long)by * C * step;
+        if (!d3) return p + (long long)by * step;
+        const int q = (t - l) / C, j = t - l - q * C, jn = j + by;
+        if (jn >= 0 && jn < C) return p + (long long)by * step;
+        const int qn = (jn < 0 ? link[q].x : link[q].y) - 1;
+        return qn < 0 ? -1 : ((long long)(qn * C + ((jn + C) % C) + l) * 64 + l) * NR + k;
+      };
+      unsigned cw = 0;
+      for (int e = 0; e < nd; ++e) {
+        const int d = ax[e];
+        if (d >= hi.dim) {
+          cw |= (CC_NODN | CC_NOUP) << (4 * e);
+          continue;
+        }
+        const int sg = ((o >> d) & 1) ? -1 : 1;
+        auto cell = [&](int by) {  // the neighbour's cell, or -1
+          const int y = x[d] + by * sg;
+          if (y < 0 || y >= hi.n[d]) return -1;
+          const int n = c + by * sg * st[d];
+          return hi.active[n] ? n : -1;
+        };
+        auto iso = [&](int cc) {  // the slot of cell cc's isothermal upwind face, or -1
+          const int slot = hi.bslot[(size_t)cc * 6 + 2 * d + (sg > 0 ? 0 : 1)];
+          return slot >= 0 && hi.bc_kind[hi.bf_bc[slot]] == BTE_BC_ISOTHERMAL ? slot : -1;
+        };
+        unsigned f = 0;
+        const int dn = cell(1), up = cell(-1);
+        if (dn < 0) f |= CC_NODN;
+        else if (pos[dn] != expect(e, 1)) return false;
+        int slot = -1;
+        if (up < 0) {
+          f |= CC_NOUP;
+          slot = iso(c);
+        } else {
+          if (pos[up] != expect(e, -1)) return false;
+          const int uu = cell(-2);
+          if (uu < 0) {
+            f |= CC_NOUU;
+            slot = iso(up);
+          } else if (pos[uu] != expect(e, -2)) {
+            return false;
+          }
+        }
+        if (slot >= 0) {
+          f |= CC_ISO;
+          int& ws = out.wslot[(size_t)o * nd + e];
+          if (ws < 0) ws = slot;
+          if (hi.bc_T[hi.bf_bc[ws]] != hi.bc_T[hi.bf_bc[slot]]) return false;
+        }
+        cw |= f << (4 * e);
+      }
+      unsigned& w = code[(size_t)t * 64 + l];
+      if (w == CC_IDLE) w = none;
+      w = (w & ~(((1u << (4 * nd - 1)) * 2 - 1) << (4 * k * nd))) | cw << (4 * k * nd);
+    }
+  }
+  return true;
 }
 
 }  // namespace bte

@@ -80,6 +80,7 @@ struct Schedule {
   int ax[3] = {0, 1, 2};             // grid axis of the kernel's step, lane and plane axes
   int n_pl = 0;                      // planes (cells along the plane axis)
   int n_per = 0;                     // plane periods of kC2 steps (the most of any octant)
+  std::vector<int> per_b;            // [n_oct][n_per] block of each plane period (-1: none), sweep orientation
   std::vector<int> xpre;             // [n_oct][n_pl][64*NR] step-axis wall face of the first column's cells (-1)
   std::vector<int> gpre;             // [n_oct][T + n_per] lane-axis wall face + 1 of lane 0's row 0 at each
                                      // step (0: none), then the plane + 1 of each plane period
@@ -130,6 +131,21 @@ bool build_schedule_3r(const HostInst& hi, const Plan& plan, Schedule& s, std::s
 // the ordinate enters through (its boundary-face slot). A position of no cell
 // has kNoCell as its first code.
 std::vector<int> corr_stencil(const HostInst& hi, const Schedule& s);
+
+// The marching correction kernel's tables (one-strip layouts, s.nS == 1), from
+// the same neighbour rules: boundary codes per lane-step, the isothermal wall
+// of each octant and axis, the units of a group, and in 3D the periods beside
+// each. Returns false when some neighbour of a cell is not where the layout's
+// fixed distances and block links put it, or when the isothermal walls an
+// octant enters through along one axis differ in temperature (the kernel keeps
+// one value per axis: a load per step would wait for its prefetches).
+struct CorrTables {
+  std::vector<unsigned> code;
+  std::vector<int> wslot;
+  std::vector<int2> unit, link;
+  int n_unit = 0, seg = 1, tail = 1;
+};
+bool corr_tables(const HostInst& hi, const Schedule& s, int n_grp, CorrTables& out);
 
 // sum over incoming directions of w |s . n| for a face normal to axis d.
 double half_range(const std::vector<Ordinate>& ords, int d);
