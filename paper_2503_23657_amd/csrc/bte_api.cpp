@@ -225,6 +225,9 @@ struct bte_ctx {
   void* d_zg = nullptr;
   long long zg_stride = 0;
   int* d_counters = nullptr;
+  FilmInst* d_film = nullptr;          // 1D films swept in one launch per chunk (NULL: not these)
+  int film_cells = 0;                  // longest of them
+  bool film_reflects = false;          // some end is a diffuse or specular wall
   FinInst* d_fin_f = nullptr;
   FinInst* d_fin_a = nullptr;
   int2* d_fblocks = nullptr;
@@ -735,6 +738,32 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
     HIPCHK(pp.upload(&pb, b));
     h->d_gt_f = pa;
     h->d_gt_a = pb;
+  }
+  // 1D films in one launch per chunk (bte_film.hip): unmasked, first-order
+  // faces, one ordinate per group, within the kernel's registers and LDS. One
+  // workgroup then sweeps a whole film; the sweep kernel's single active lane
+  // takes ten times as long even where that workgroup has a thousand ordinates
+  h->d_film = nullptr;
+  h->film_cells = 0;
+  h->film_reflects = false;
+  if (h->dim == 1 && pl.G == 1 && h->order == 1) {
+    bool ok = true;
+    std::vector<FilmInst> film;
+    for (const auto& I : h->inst) {
+      const int n = I.hi.ncell;
+      ok = ok && I.hi.n_active == n && n <= kFilmCells;
+      h->film_cells = std::max(h->film_cells, n);
+      FilmInst f{};
+      for (int e = 0; e < 2 && ok; ++e) {
+        f.slot[e] = I.hi.bslot[(size_t)(e ? n - 1 : 0) * 6 + e];
+        f.kind[e] = I.hi.bc_kind[I.hi.bf_bc[f.slot[e]]];
+        f.inv_half[e] = 1.0 / half_range(h->ords, 0);
+        if (f.kind[e] != BTE_BC_ISOTHERMAL) h->film_reflects = true;
+      }
+      film.push_back(f);
+    }
+    ok = ok && film_lds_bytes((long long)es, film_cpl(h->film_cells), n_grp_inst) <= kFilmLds;
+    if (ok) HIPCHK(pp.upload(&h->d_film, film));
   }
   // LDS carve-up
   const int R = L3 ? 1 : pl.R, P = pl.P, G = pl.G, Cc = pl.C;
@@ -1301,8 +1330,32 @@ bte_status enqueue_corr(bte_ctx* h, hipStream_t st) {
   return BTE_OK;
 }
 
+// n iterations of 1D films, as enqueue_chunk, in one launch.
+bte_status enqueue_film(bte_ctx* h, bool adj, int n, const bte_opts& o, hipStream_t st) {
+  FilmArgs a;
+  a.inst = adj ? h->d_inst_a : h->d_inst_f;
+  a.fin = adj ? h->d_fin_a : h->d_fin_f;
+  a.walls = h->d_film;
+  a.grp_i = adj ? h->d_gi_a : h->d_gi_f;
+  a.grp_t = adj ? h->d_gt_a : h->d_gt_f;
+  a.n_grp = (int)h->gs.band.size();
+  a.g_split = (int)(std::find(h->gs.oct.begin(), h->gs.oct.end(), 1) - h->gs.oct.begin());
+  a.n_iter = n;
+  a.flags = adj ? FIN_ADJ : 0;
+  a.tol_T = o.tol_T;
+  a.tol_q = adj ? 1.0 : o.tol_q;
+  a.B = h->B;
+  a.rows = h->ubf_rows;
+  a.src = h->d_spec_src;
+  a.inv_wq = h->d_spec_iwq;
+  a.grp_ob = h->inst[0].d_grp_ob;
+  HIPCHK(launch_film_chunk(h->precision, a, (int)h->inst.size(), film_cpl(h->film_cells), st));
+  return BTE_OK;
+}
+
 // n iterations; the last one checks convergence, the last two carry the flux.
 bte_status enqueue_chunk(bte_ctx* h, bool adj, int n, const bte_opts& o, hipStream_t st) {
+  if (h->d_film && !(adj && h->film_reflects)) return enqueue_film(h, adj, n, o, st);
   const bool second = !adj && h->order == 2;
   const int nq = second ? std::max(3, 1 + h->dim) : 1 + h->dim;
   for (int k = 0; k < n; ++k) {

@@ -371,6 +371,39 @@ struct InitArgs {
   int adjoint;
 };
 
+// 1D films (bte_film.hip): the iterations of a chunk in one launch.
+struct FilmInst {
+  int kind[2];               // BTE_BC_* of the -x and +x end
+  int slot[2];               // their boundary-face slots
+  double inv_half[2];        // 1 / sum_{in} w |s.n|
+};
+struct FilmArgs {
+  const InstDev* inst;
+  const FinInst* fin;
+  const FilmInst* walls;     // [n_inst]
+  const int4* grp_i;         // [n_inst][n_grp]
+  const void* grp_t;         // [n_inst][n_grp][grp_stride(1)]
+  int n_grp;                 // groups of an instance
+  int g_split;               // first group of octant 1
+  int n_iter;
+  int flags;                 // FIN_ADJ
+  double tol_T, tol_q;
+  int B, rows;               // bands; inflow-table rows per band
+  const int2* src;           // specular walls, as in SpecArgs
+  const double* inv_wq;
+  const int2* grp_ob;        // [2][B]
+};
+constexpr int kFilmConst = 8;           // values per group kept in LDS
+constexpr int kFilmLds = 150 * 1024;    // most LDS a launch may ask for (160 KiB per CU)
+constexpr int kFilmCells = 1024;        // longest film: 16 cells per lane
+// cells per lane (a power of two) and waves; with 16 cells per lane, eight
+// waves: their state needs more than the 128 registers sixteen waves leave
+__host__ __device__ constexpr int film_cpl(int n) { return n <= 64 ? 1 : n <= 128 ? 2 : n <= 256 ? 4 : n <= 512 ? 8 : 16; }
+__host__ __device__ constexpr int film_waves(int cpl) { return cpl == 16 ? 8 : 16; }
+__host__ __device__ constexpr long long film_lds_bytes(long long es, int cpl, int n_grp) {
+  return 8ll * 64 * (film_waves(cpl) * (cpl < 4 ? 4 : cpl) + cpl) + n_grp * (kFilmConst + 1) * es;
+}
+
 struct UbfInitArgs {
   void* ubf;                 // [B][rows][n_bface]
   int n_bface, B;            // B: bands x rows

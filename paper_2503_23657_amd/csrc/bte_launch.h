@@ -31,6 +31,8 @@ hipError_t launch_sweep3r(int prec, int NR, int P, int nacc, int mode, const Swe
 int sweep3r_blocks_per_cu(int prec, int NR, int P, int nacc, int mode, int block, size_t lds);
 
 hipError_t launch_finalize(int prec, const FinArgs& a, const FinInst* fi, hipStream_t st);
+// n_iter source iterations of every instance of a handle of 1D films
+hipError_t launch_film_chunk(int prec, const FilmArgs& a, int n_inst, int cpl, hipStream_t st);
 hipError_t launch_wall_update(int prec, const WallArgs& a, int n_oct, hipStream_t st);
 hipError_t launch_spec_update(int prec, const SpecArgs& a, hipStream_t st);
 hipError_t launch_plane_tables(const PlaneOrder& po, int ncell, int n_oct, const int* pos_c, int* pos, int* cell_of,
