@@ -542,7 +542,15 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
     nbi.push_back(I.n_fblocks);
     h->fin_f[k].blockpart = h->fin_a[k].blockpart = I.d_blockpart;
     HIPCHK(pp.upload(&I.d_in_tab, S.in_tab));
-    HIPCHK(pp.upload(&I.d_chunk_fl, S.chunk_fl));
+    std::vector<int> cfl(S.chunk_fl);
+    if (rows) {
+      const int nch = S.T / kC2;
+      for (size_t s1 = 0; s1 < cfl.size() / (nch + 1); ++s1)
+        for (int c = 0; c < nch; ++c)
+          cfl[s1 * (nch + 1) + c] |=
+              (S.in_chunk[s1 * (nch + 1) + c + 1] - S.in_chunk[s1 * (nch + 1) + c] + 63) / 64 << 8;
+    }
+    HIPCHK(pp.upload(&I.d_chunk_fl, cfl));
     HIPCHK(pp.upload(&I.d_out_base, S.out_base));
     HIPCHK(pp.upload(&I.d_pre_slot, S.pre_slot));
     HIPCHK(pp.upload(&I.d_ofk, S.ofk));
@@ -570,7 +578,14 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
     if (S.l3r) {
       HIPCHK(pp.upload(&I.d_xpre, S.xpre));
       HIPCHK(pp.upload(&I.d_gpre, S.gpre));
-      HIPCHK(pp.upload(&I.d_out_tab, S.out_tab));
+      // the entries by their place in the kernel's staging
+      std::vector<int> otab(S.out_tab);
+      for (int& e : otab)
+        if (e > 0) {
+          const int idx = (e - 1) >> 2, row = 64 * S.NR;
+          e = (idx / row * stage_row(S.NR, (int)es) + idx % row) << 3 | ((e - 1) & 3) << 1 | 1;
+        }
+      HIPCHK(pp.upload(&I.d_out_tab, otab));
       HIPCHK(pp.upload(&I.d_out_chunk, S.out_chunk));
     }
     std::vector<int2> gob(n_oct * h->B);
@@ -789,7 +804,7 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
     sa.lds_out = (int)off;
     off += R3 ? 0 : al((size_t)P * R * o_max * es);
     sa.lds_stage = (int)off;
-    h->lds_stage_plane = al((size_t)P * R * kC2 * (64 * pl.NR + 32 / es) * es);  // rows padded by 8 dwords
+    h->lds_stage_plane = al((size_t)P * R * kC2 * stage_row(pl.NR, (int)es) * es);
     off += (size_t)std::max(2, h->nacc_max) * h->lds_stage_plane;
     sa.lds_total = (int)off;
     if (off > 160 * 1024 - 64) {

@@ -70,6 +70,9 @@ constexpr uint32_t F2_INOFF_MASK = 0xFFu;
 // and replace the rows' x-upwind values; no other inflow in the lane-step
 constexpr uint32_t F2_XSTART = 1u << 28;
 // per-chunk flags of the 1D/2D schedule
+// elements of one staged step of a wave (64 lanes of nr rows, padded by 8
+// dwords so that the write-out's reads hit distinct banks)
+__host__ __device__ constexpr int stage_row(int nr, int es) { return 64 * nr + 32 / es; }
 constexpr int CF2_IN = 1;       // some inflow entry in the chunk
 constexpr int CF2_INY_UP = 2;   // some y-inflow on a row k >= 1 of a lane
 constexpr int CF2_OUT = 4;      // some outflow entry in the chunk
@@ -158,7 +161,8 @@ struct InstDev {
   int n_strip;              // strips of 64*nr rows
   int in_E;                 // entries per chunk row of in_tab (multiple of 64, <= 256)
   const int* in_tab;        // [n_oct][R][T/kC2 + 2][in_E] inflow face slot of each stream entry (-1 pad)
-  const int* chunk_fl;      // [n_oct][R][T/kC2 + 1] CF2_* flags of each chunk (0 pad)
+  const int* chunk_fl;      // [n_oct][R][T/kC2 + 1] CF2_* flags of each chunk (0 pad), and from bit 8 on
+                            //   its rows of 64 inflow entries
   // second-order faces (rows-per-lane layouts, one ordinate per group): the
   // deferred correction of each group's source, in its octant's skewed layout
   void* corr;               // [n_grp][pos_per_oct] sweep precision
@@ -171,7 +175,7 @@ struct InstDev {
   const int* gpre;          // [n_oct][T + n_per] lane-axis wall face + 1 of lane 0's row 0 at each step
                             //   (0: none), then the plane + 1 of each plane period (0: none)
   const int* out_tab;       // [n_oct][T/kC2 + 2][out_E] outflow entries of each chunk, read from the staging
-                            //   ((((u*64 + l)*nr + k) << 2 | kernel axis) + 1, 0 pad)
+                            //   (element of the wave's staged chunk << 3 | kernel axis << 1 | 1, 0 pad)
   const int* out_chunk;     // [n_oct][T/kC2 + 1] stream offset of each chunk's first outflow entry
   int out_E;                // entries per chunk row of out_tab (multiple of 64, <= 256)
 };

@@ -43,6 +43,7 @@
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "bte_device.h"
 #include "bte_kutil.h"
@@ -54,6 +55,19 @@ namespace s2d {
 // the kernel's lambdas are inlined whatever their size: the chunk steps index
 // register arrays with the step number, which must fold to a constant
 #define BTE_INL __attribute__((always_inline))
+
+// f(0), ..., f(N - 1) with the index as a type: one instantiation per index, so
+// that an index into a register array is a constant from the start (a loop
+// with a uniform condition inside may otherwise keep its run-time index, which
+// puts the array, and all a lambda captures, into scratch)
+template <typename F, int... I>
+__device__ __forceinline__ void unrolled_seq(F& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(F& f) {
+  unrolled_seq(f, std::make_integer_sequence<int, N>());
+}
 
 template <typename T, int N>
 struct Vec {
@@ -92,6 +106,20 @@ __device__ __forceinline__ int lanes_below(unsigned long long m) {
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt, expcnt unchanged
   __builtin_amdgcn_s_barrier();
+}
+
+// one of three values by bits 1 and 2 of e; by value and with opaque copies (a
+// select between variables a lambda captured becomes an indexed read of a
+// stack copy)
+template <typename T>
+__device__ __forceinline__ T one_of(int e, T a, T b, T c) {
+  asm("" : "+v"(a));
+  asm("" : "+v"(b));
+  asm("" : "+v"(c));
+  T w = a;
+  if (e & 2) w = b;
+  if (e & 4) w = c;
+  return w;
 }
 
 constexpr int min_c(int a, int b) { return a < b ? a : b; }
@@ -161,7 +189,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
   // staged row stride (elements) and record row stride (ints): 8 dwords of
   // padding put the (step, lane) pairs a write-out read takes in one LDS pass
   // on distinct banks
-  constexpr int RS = 64 * NR + 32 / (int)sizeof(T);
+  constexpr int RS = stage_row(NR, (int)sizeof(T));
   constexpr int CS = 64 + 8;
   constexpr int kEPL = 4;                     // inflow entries per lane per chunk (<= 256)
   extern __shared__ __align__(16) char lds[];
@@ -394,7 +422,10 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
     // 3D inflow chunks: the next step's stream values of the lane's rows
     // (step, lane, plane axis), read from LDS one step ahead
     T pin[L3 ? NR : 1][3];
-    int qL = 0, qS = 0, pL1 = 0, pS1 = 0;  // period and plane + 1 of the next load / store
+    // plane + 1 of the next load (period ch + 2 - l/kC2 at the end of chunk ch)
+    // and of the three before it: the store's period is that of two loads ago
+    // for the first lane of kC2, else of three loads ago
+    int qL = 0, pL1 = 0, pLa = 0, pLb = 0, pLc = 0;
     const rsrc_t GPR = mkrsrc(L3 ? gp(I.gpre) + (size_t)o * (T_steps + I.n_per) : nullptr,
                               L3 ? (unsigned)(T_steps + I.n_per) * 4u : 0u);
     auto ptab = [&](int q) BTE_INL { return bld<int>(GPR, q >= 0 && q < I.n_per ? (T_steps + q) * 4 : kOOB); };
@@ -405,13 +436,14 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
 #pragma unroll
         for (int k = 0; k < NR; ++k) zreg[u][k] = T(0);
       qL = -(lane / kC2);
-      xl = ldv_glc<VR>(ZRR, xoff(ptab(qL)), 0);
+      pLc = ptab(qL - 1);
+      pLb = ptab(qL);
+      xl = ldv_glc<VR>(ZRR, xoff(pLb), 0);
       ++qL;
-      xn = ldv_glc<VR>(ZRR, xoff(ptab(qL)), 0);
+      pLa = ptab(qL);
+      xn = ldv_glc<VR>(ZRR, xoff(pLa), 0);
       ++qL;
       pL1 = ptab(qL);
-      qS = -((lane + kC2 - 1) / kC2);
-      pS1 = ptab(qS);
     }
 
     // ghost values (lane 0's upwind row) and ring-write offsets (lane 63's top
@@ -459,8 +491,11 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
     if constexpr (!L3) chunk_cols();
     // per-chunk flags (CF2_*), uniform: scalar loads from read-only memory
     const CAS int* CFL = cp(I.chunk_fl) + slot * (nch + 1);
+    // bits 8 and up: rows of 64 inflow entries
     int cfl = CFL[0];
-    int cfl_next = CFL[nch > 0 ? 1 : 0];
+    int cfl_next = CFL[min(1, nch)];
+    int cfl_2 = CFL[min(2, nch)], cfl_3 = CFL[min(3, nch)];
+    int in_rows = 0;  // most rows of the three chunks ahead
     // let the loads above land before the chunk loop: the loop's waits are
     // counted for its steady state (a whole chunk of loads after each slot's),
     // which a partly drained prologue would otherwise cut to its own shorter
@@ -491,6 +526,12 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
     static_assert(MB >= 1 && PAIRS % MB == 0 && (!PIPE || MB * NB == PAIRS),
                   "write-out batches must tile the pairs exactly");
     const int t_wo = p * 64 + lane;
+    // steps after which batch b is read from LDS and, some steps later (an LDS
+    // read of 16 bytes per lane by every wave takes about two steps), stored:
+    // one batch after steps 0 and 3, two after 0, 3 and 6, four after 0, 2, 4,
+    // 6 and 7
+    auto wo_at = [](int b) constexpr { return NB == 4 ? 2 * b : 3 * b; };
+    auto wo_gap = [](int b) constexpr { return NB == 4 ? (b == 3 ? 1 : 2) : 3; };
     int wvv[MB];
     // the constants of the P waves' ordinates: in registers while there are
     // few, else one per lane of a register and taken with readlane
@@ -594,40 +635,58 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
     //      the wave is the lane's own value) and written to the out-stream
     //      after the chunk; oe holds the entries of chunk `c`, och its stream
     //      offset, and the entries of the chunk after are loaded behind them
+    //      (rows of 64 entries past a chunk's own are skipped by a uniform
+    //      branch: most chunks have the few entries of the lane axis's end.
+    //      The chunk's vector memory instructions bound the 3D sweep: with
+    //      these rows, the inflow's empty ones and the second read of the
+    //      period table skipped, the 92x90x69 domain in FP32 went from 2997 to
+    //      2744 us a sweep)
     constexpr int kOPL = 4;  // entries per lane per chunk (<= 256 per chunk)
     int oe[kOPL];
-    int och = 0;
-    const int NOE = L3 ? I.out_E >> 6 : 0;
+    int och = 0, och1 = 0, och2 = 0;  // offsets of chunk c, c + 1, c + 2
     const rsrc_t OTR = mkrsrc(L3 ? gp(I.out_tab) + (size_t)o * (nch + 2) * I.out_E : nullptr,
                               L3 ? (unsigned)((nch + 2) * I.out_E) * 4u : 0u);
     const CAS int* OCH = L3 ? cp(I.out_chunk) + (size_t)o * (nch + 1) : nullptr;
-    auto out_load = [&](int c) BTE_INL {
-      // entry m of the lane at (c * out_E + m * 64 + lane) * 4; an entry
-      // past the row (m >= NOE) gets an offset past the buffer (uniform, so
-      // no per-lane mask is kept)
+    auto out_load = [&](int c, int rows) BTE_INL {
+      // entry m of the lane at (c * out_E + m * 64 + lane) * 4
       const int lo = (c * I.out_E + lane) * 4;
-#pragma unroll
-      for (int m = 0; m < kOPL; ++m) oe[m] = bld<int>(OTR, lo + (m < NOE ? m * 256 : kOOB));
+      auto row = [&](auto m) BTE_INL {
+        if (m == 0 || m < rows) oe[m] = bld<int>(OTR, lo + m * 256);
+      };
+      unrolled<kOPL>(row);
     };
+    auto out_rows = [](int a, int b) { return (b - a + 63) >> 6; };
     if constexpr (L3) {
-      out_load(0);
-      och = OCH[0];
-    }
-    auto emit = [&](int c) BTE_INL {
-      const T* sb = stage + (size_t)(PIPE ? (c & 1) : 0) * plane_sz + (size_t)(p * R + r) * kC2 * RS;
-      // the axis weight of an entry by arithmetic (a select between the
-      // three would be turned into an indexed read of a stack copy)
-      const T wA = wo0[0], wB = wo1[0] - wo0[0], wC = wo2[0] - wo1[0];
 #pragma unroll
-      for (int m = 0; m < kOPL; ++m) {
-        const int e = oe[m] - 1;  // stored + 1 (0: no entry, also what a read past the table gives)
-        const int idx = e >> 2, d = e & 3;
-        const T v = sb[(e >= 0 ? idx / (64 * NR) : 0) * RS + (idx & (64 * NR - 1))];
-        const T w = fma(T(d >= 2), wC, fma(T(d >= 1), wB, wA));
-        bst(w * v, OUR, e >= 0 ? (och + m * 64 + lane) * (int)sizeof(T) : kOOB);
-      }
-      out_load(c + 1);
-      och = OCH[min(c + 1, nch)];
+      for (int m = 0; m < kOPL; ++m) oe[m] = 0;
+      och = OCH[0];
+      och1 = OCH[min(1, nch)];
+      och2 = OCH[min(2, nch)];
+      out_load(0, out_rows(och, och1));
+    }
+    T ev[kOPL];
+    auto emit_read = [&](int c) BTE_INL {
+      const T* sb = stage + (size_t)(PIPE ? (c & 1) : 0) * plane_sz + (size_t)(p * R + r) * kC2 * RS;
+      const int rows = out_rows(och, och1);
+      auto row = [&](auto m) BTE_INL {
+        if (m == 0 || m < rows) ev[m] = sb[(unsigned)oe[m] >> 3];
+      };
+      unrolled<kOPL>(row);
+    };
+    auto emit_store = [&](int c) BTE_INL {
+      const int rows = out_rows(och, och1);
+      auto row = [&](auto m) BTE_INL {
+        if (m == 0 || m < rows) {
+          const int e = oe[m];  // staging index << 3 | axis << 1 | 1 (0: no entry, also what a read past the table gives)
+          const T w = one_of(e, wo0[0], wo1[0], wo2[0]);
+          bst(w * ev[m], OUR, (e & 1) ? (och + m * 64 + lane) * (int)sizeof(T) : kOOB);
+        }
+      };
+      unrolled<kOPL>(row);
+      out_load(c + 1, out_rows(och1, och2));
+      och = och1;
+      och1 = och2;
+      och2 = OCH[min(c + 3, nch)];
     };
 
     // ---- one chunk of kC2 steps; IN: 0 no flagged inflow entries in the
@@ -644,6 +703,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
       T* stg0 = stage + (size_t)(PIPE ? bufi : 0) * plane_sz + (size_t)(p * R + r) * kC2 * RS;
       int* scw = scid + (bufi * R + r) * kC2 * CS;
       int out_cnt = 0;
+      in_rows = max(max(cfl_next, cfl_2), cfl_3) >> 8;
       // the chunk's prefetch: 3D through the fixed views with a uniform offset
       // (fewer scalar registers live), 1D/2D through views based at the first
       // position prefetched in the chunk (immediate offsets per step)
@@ -690,8 +750,9 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
       };
       if constexpr (L3 && IN == 2) in_read(RR[0]);
 
-      auto step = [&](const int u) BTE_INL {
-        const int sl = u % KD;
+      auto step = [&](auto u_tag) BTE_INL {
+        constexpr int u = decltype(u_tag)::value;
+        constexpr int sl = u % KD;
         const int2 rec = RR[sl];
         // both halves of the record stay live until here, whatever the body
         // uses: a half the body ignores would otherwise free its register
@@ -918,18 +979,26 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
 
         // ---- the previous chunk's write-out
         if constexpr (PIPE) {
-          if (u % 2 == 0 && u / 2 < NB) wo_read(u / 2, ch - 1);
-          if (u % 2 == 1 && u / 2 < NB) wo_store(ch > 0);
+          auto batch = [&](auto b) BTE_INL {
+            if constexpr (u == wo_at(b) + wo_gap(b)) wo_store(ch > 0);
+            if constexpr (u == wo_at(b)) wo_read(b, ch - 1);
+          };
+          unrolled<NB>(batch);
           // and its outflows
-          if (L3 && u == kC2 - 3 && ch > 0) emit(ch - 1);
+          if constexpr (L3 && u == kC2 - 4)
+            if (ch > 0) emit_read(ch - 1);
+          if constexpr (L3 && u == kC2 - 2)
+            if (ch > 0) emit_store(ch - 1);
         }
         // ---- inflow pipeline, one stream row per step at the chunk's end,
         //      rows in descending order: values of chunk ch+1 to LDS (a row
         //      past the stream writes row 0, which row 0's own write then
         //      replaces: no branch); gather chunk ch+2's values (a slot of -1
         //      reads 0); load the face slots of chunk ch+3
-        if (u >= kC2 - kEPL) {
-          const int m = kC2 - 1 - u;
+        //      (rows no chunk ahead has entries in are skipped by a uniform branch)
+        if constexpr (u >= kC2 - kEPL)
+        if (kC2 - 1 - u < in_rows) {
+          constexpr int m = kC2 - 1 - u;
           // (3D: stored scaled into the lane's variable, read once per use)
           my_inb[((ch + 1) & 1) * E + (m < NE ? m : 0) * 64 + lane] = L3 ? inval[m] * den[0] : inval[m];
           inval[m] = bld<T>(UBR, slot_n[m] * (int)sizeof(T));
@@ -945,28 +1014,34 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
         if (MODE == M2_TAUGRAD) RXF[sl] = ldv<VX>(rf, lo_xq, (sb + u * 64) * (int)sizeof(VX));
         if (MODE == M2_SECOND) RC[sl] = ldv<VR>(rc, lo_xc, (sb + u * 64) * (int)sizeof(VR));
       };
-#pragma unroll
-      for (int u = 0; u < kC2; ++u) step(u);
+      unrolled<kC2>(step);
 
       // ---- end of chunk: the staged sums, the ring and the outflow entries
       //      of every wave are complete
+      VR xs;
+      if constexpr (L3)  // (the lane's last column is chunk step u = l - 1 mod kC2; own values: no barrier)
+        xs = *reinterpret_cast<const VR*>(stg0 + ((lane + kC2 - 1) & (kC2 - 1)) * RS + lane * NR);
+      // one strip: the ring holds the first row's wall values only
+      if (!L3 && !ring_w) chunk_cols();
       lds_barrier();
       if constexpr (L3) {
         // the block's last column of this chunk's period to its plane; the
         // column-0 value of the chunk after the next one (its plane was
         // written at least a chunk ago: four or more planes)
-        // (the lane's last column is chunk step u = l - 1 mod kC2)
-        const VR xs = *reinterpret_cast<const VR*>(stg0 + ((lane + kC2 - 1) & (kC2 - 1)) * RS + lane * NR);
-        stv(xs, ZRR, xoff(pS1), 0);
-        pS1 = ptab(++qS);
+        stv(xs, ZRR, xoff((lane & (kC2 - 1)) == 0 ? pLb : pLc), 0);
         xl = xn;
         xn = ldv_glc<VR>(ZRR, xoff(pL1), 0);
+        pLc = pLb;
+        pLb = pLa;
+        pLa = pL1;
         pL1 = ptab(++qL);
       }
       // flags of the next chunk were read a chunk ago; read the one after
       cfl = cfl_next;
-      cfl_next = CFL[min(ch + 2, nch)];
-      chunk_cols();
+      cfl_next = cfl_2;
+      cfl_2 = cfl_3;
+      cfl_3 = CFL[min(ch + 4, nch)];
+      if (L3 || ring_w) chunk_cols();
       if (OUT) {
         // flush this chunk's outflow entries (at most 256)
 #pragma unroll
@@ -980,7 +1055,10 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
       if constexpr (!PIPE) {
         // single-buffered staging: write the chunk (and its outflows) out
         // now, then wait for every reader before the next chunk stages again
-        if constexpr (L3) emit(ch);
+        if constexpr (L3) {
+          emit_read(ch);
+          emit_store(ch);
+        }
 #pragma unroll
         for (int b = 0; b < PAIRS / MB; ++b) {
           wo_read(b, ch);
@@ -1001,7 +1079,8 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
     using I2 = std::integral_constant<int, 2>;
     using B0 = std::integral_constant<bool, false>;
     using B1 = std::integral_constant<bool, true>;
-    auto kind = [](int fl) {
+    auto kind = [](int fl8) {
+      const int fl = fl8 & 0xFF;
       return fl == 0 ? 0 : (fl == CF2_XST ? 3 : ((fl & CF2_INY_UP) ? 2 : 1));
     };
     // a run's entry copies the ring between the runs' registers; draining
@@ -1050,7 +1129,10 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
         wo_read(b, nch - 1);
         wo_store(nch > 0);
       }
-      if (L3 && nch > 0) emit(nch - 1);
+      if (L3 && nch > 0) {
+        emit_read(nch - 1);
+        emit_store(nch - 1);
+      }
     }
 
     if (MODE == M2_TAUGRAD) {
