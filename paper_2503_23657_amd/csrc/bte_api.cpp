@@ -151,6 +151,9 @@ struct Inst {
   void* d_part = nullptr;
   int n_part = 0;   // indices of a partial-sum plane (cells, and the padding of its blocks)
   int* d_cell_of = nullptr;  // [n_part] cell of each plane index (NULL: itself)
+  int part_bs = 0, part_cs = 0;  // plane-index steps of a block of kC2 columns and of a column
+  int2* d_per_base = nullptr;    // 3D rows layout: see period_bases
+  int per_stride = 0;
   int part_ld = 0;  // cells per job in a partial-sum plane (n_part padded to cell blocks)
   int part_jg = 0;  // log2 of the jobs per group of a plane
   void* d_store = nullptr;
@@ -345,6 +348,27 @@ PlaneOrder plane_order(const HostInst& hi, const Schedule& S) {
   return po;
 }
 
+// 3D: the part of a plane index that a plane period fixes (its block of kC2
+// columns, bs apart, and its plane, ps apart; an octant that runs an axis
+// backwards counts from its end, with the columns of the last block inside the
+// grid as its first) and the columns of its block, 0 for no period. Entry i of
+// an octant is period i - kPerPad; the sweep reads up to T / kC2.
+std::vector<int2> period_bases(const Schedule& S, const PlaneOrder& po, int bs, int ps, int& stride) {
+  const int n_per = S.n_per;
+  stride = S.T / kC2 + kPerPad + 1;
+  std::vector<int2> pb((size_t)S.n_oct * stride, make_int2(0, 0));
+  for (int o = 0; o < S.n_oct; ++o)
+    for (int q = 0; q < n_per; ++q) {
+      const int b = S.per_b[(size_t)o * n_per + q];
+      if (b < 0) continue;
+      int pl = S.gpre[(size_t)o * (S.T + n_per) + S.T + q] - 1;
+      if ((o >> S.ax[2]) & 1) pl = po.n[2] - 1 - pl;
+      pb[(size_t)o * stride + q + kPerPad] =
+          make_int2(((o >> S.ax[0]) & 1 ? -b : b) * bs + pl * ps, std::min(kC2, po.n[0] - b * kC2));
+    }
+  return pb;
+}
+
 // (Re)build everything that depends on the plan: schedules, group tables and
 // the plan-dependent arrays.
 bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
@@ -532,6 +556,17 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
     } else {
       HIPCHK(pp.upload(&I.d_pos, S.pos));
     }
+    // the sweep's own form of the plane index: column blocks and columns, and
+    // in 3D the part of every plane period's block and plane
+    I.part_bs = blocks ? po.nr * po.n[2] * kC2 : kC2 * (L3 ? po.st[0] : 1);
+    I.part_cs = blocks || !L3 ? 1 : po.st[0];
+    I.d_per_base = nullptr;
+    I.per_stride = 0;
+    if (rows && L3) {
+      const std::vector<int2> pb = period_bases(S, po, I.part_bs, blocks ? po.nr * kC2 : po.st[2], I.per_stride);
+      HIPCHK(pp.upload(&I.d_per_base, pb));
+      h->part_extra += al256(pb.size() * sizeof(int2));
+    }
     if (!rows) {
       HIPCHK(pp.upload(&I.d_in_slot, S.in_slot));
       HIPCHK(pp.upload(&I.d_in_chunk, S.in_chunk));
@@ -691,6 +726,10 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
       d.outv = I.d_outv;
       d.part = I.d_part;
       d.n_part = I.n_part;
+      d.part_bs = I.part_bs;
+      d.part_cs = I.part_cs;
+      d.per_base = I.d_per_base;
+      d.per_stride = I.per_stride;
       d.cell_of = I.d_cell_of;
       d.part_ld = I.part_ld;
       d.part_jg = I.part_jg;
@@ -793,12 +832,12 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
     // temperature-only sweep)
     int E = 64;
     for (auto& I : h->inst) E = std::max(E, I.sch.in_E);
-    // (the 3D rows layout has no strip ring and emits its outflows from the
-    // staging: neither takes LDS)
+    // (the 3D rows layout has no strip ring, forms its plane indices from the
+    // period table and emits its outflows from the staging: none takes LDS)
     sa.lds_zring = (int)off;
     off += R3 ? 0 : al((size_t)P * R * (W_max + 1) * G * es);
     sa.lds_cid = (int)off;
-    off += al((size_t)2 * R * kC2 * (64 + 8) * 4);  // records, rows padded to 72 ints
+    off += R3 ? 0 : al((size_t)2 * R * kC2 * (64 + 8) * 4);  // records, rows padded to 72 ints
     sa.lds_in = (int)off;
     off += al((size_t)P * R * 2 * E * es);
     sa.lds_out = (int)off;

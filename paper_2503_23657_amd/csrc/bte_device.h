@@ -143,6 +143,13 @@ struct InstDev {
   // columns of a row side by side; cell_of maps a plane index to its cell
   // (-1: padding), NULL: the cell index itself. The sched records hold the
   // plane index of the lane's first row, dyo the index step to the next row.
+  // Column x, row y (and in 3D plane z) of the kernel axes sits at
+  // (x / kC2) * part_bs + (x % kC2) * part_cs + y * |dyo| (+ z's part).
+  // per_base (3D): {plane-index part of a period's block and plane, columns of
+  // the block}, entry i: period i - kPerPad
+  int part_bs, part_cs;
+  const int2* per_base;     // [n_oct][per_stride]
+  int per_stride;
   int n_part;               // indices of a plane
   const int* cell_of;       // [n_part]
   int part_ld;              // cells per job in a plane: n_part rounded up to a multiple of kPartBlk
@@ -233,6 +240,7 @@ struct SweepArgs {
 enum { FIN_Q = 1, FIN_CHECK = 2, FIN_ADJ = 4, FIN_QPREV = 8 };
 constexpr int kFinCells = 256;    // cells per finalize block
 constexpr int kFinThreads = 512;  // threads per finalize block: cell groups x job slices
+constexpr int kPerPad = 9;         // empty periods before the first: the last lanes' skew, and one
 constexpr int kPartBlk = 256;     // cells per block of the partial-sum planes (= kFinCells)
 static_assert(kPartBlk == kFinCells, "a finalize block reads one cell block of every job");
 

@@ -18,8 +18,10 @@
 //     column-indexed LDS ring; the ring values of a whole chunk of kC2 steps are
 //     read once per chunk into one register (lane m holds step m) and taken
 //     with readlane, so no step waits on LDS;
-//   * the per-step inputs, a record {cell of row 0, flags} and the (X, Q) pairs
-//     of the lane's rows, are stored in the skewed order and prefetched a whole
+//   * the per-step inputs, a record {plane index of row 0, flags} (3D: the
+//     flags alone, in chunks with boundary entries; but records where the
+//     angular field is kept or read) and the (X, Q) pairs of the lane's rows,
+//     are stored in the skewed order and prefetched a whole
 //     chunk ahead (half a chunk when the ring would not fit in ~96 registers)
 //     without any conditional, the schedule being padded; no load inside the
 //     chunk loop depends on another one, and no global access in it sits
@@ -178,6 +180,10 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
   // flux and second-order sweeps (eight-wave workgroups; four accumulators,
   // or the correction ring) take half a chunk: a whole one spilled to scratch
   // (a quarter chunk for the second-order flux sweep, which has both)
+  // the schedule's records are read whole in 1D/2D and by the modes that index
+  // the angular field by them; else only the flags are, and those only in
+  // chunks that have boundary entries
+  constexpr bool RECS = !L3 || MODE == M2_STORE || MODE == M2_TAUGRAD;
   constexpr int kRingRegs = 2 + NV * (int)sizeof(T) / 4 * (MODE == M2_TAUGRAD ? 2 : 1) +
                             (MODE == M2_SECOND ? NR * (int)sizeof(T) / 4 : 0);
   constexpr int KD = (L3 && NACC > 2 && MODE == M2_SECOND) ? kC2 / 4
@@ -189,8 +195,8 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
   // staged row stride (elements) and record row stride (ints): 8 dwords of
   // padding put the (step, lane) pairs a write-out read takes in one LDS pass
   // on distinct banks
-  constexpr int RS = stage_row(NR, (int)sizeof(T));
   constexpr int CS = 64 + 8;
+  constexpr int RS = stage_row(NR, (int)sizeof(T));
   constexpr int kEPL = 4;                     // inflow entries per lane per chunk (<= 256)
   extern __shared__ __align__(16) char lds[];
   __shared__ int s_job;
@@ -206,7 +212,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
   const int E = A.e_max;  // LDS inflow buffer entries per chunk (multiple of 64)
 
   T* ring = reinterpret_cast<T*>(lds + A.lds_zring);    // [P][R][W_max + 1][G] (+1: dummy slot)
-  int* scid = reinterpret_cast<int*>(lds + A.lds_cid);  // [2][R][kC2][CS]
+  int* scid = reinterpret_cast<int*>(lds + A.lds_cid);  // 1D/2D: [2][R][kC2][CS]
   T* inb = reinterpret_cast<T*>(lds + A.lds_in);        // [P*R][2][E]
   T* outb = reinterpret_cast<T*>(lds + A.lds_out);      // [P*R][o_max]
   T* stage = reinterpret_cast<T*>(lds + A.lds_stage);   // [planes][P*R][kC2][RS]
@@ -394,14 +400,24 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
     const rsrc_t RFB = MODE == M2_TAUGRAD ? mkrsrc(XF, nposs * (unsigned)sizeof(VX)) : RXB;
     const rsrc_t RCB = MODE == M2_SECOND ? mkrsrc(XC, nposs * (unsigned)sizeof(VR)) : RXB;
     const rsrc_t RSB = MODE == M2_SECOND ? mkrsrc(XS, nposs * (unsigned)sizeof(VR)) : RXB;
-    int2 RR[KD];
+    int2 RR[RECS ? KD : 1];
+    int FR[kC2];  // !RECS: the flags of a chunk's steps, if it has boundary entries
     VX RX[KD];
     VX RXF[KD];
     VR RC[KD];
+    auto load_flags = [&](int c) BTE_INL {
+      auto one = [&](auto u) BTE_INL { FR[u] = bld<int>(RRB, lo_rec + (c * kC2 + u) * 512 + 4); };
+      unrolled<kC2>(one);
+    };
     {
+      if constexpr (!RECS) {
+#pragma unroll
+        for (int u = 0; u < kC2; ++u) FR[u] = 0;
+        load_flags(0);
+      }
 #pragma unroll
       for (int u = 0; u < KD; ++u) {
-        RR[u] = ldrec_b(RRB, lo_rec, u * 64 * 8);
+        if constexpr (RECS) RR[u] = ldrec_b(RRB, lo_rec, u * 64 * 8);
         RX[u] = ldv<VX>(RXB, lo_xq, u * 64 * (int)sizeof(VX));
         if (MODE == M2_TAUGRAD) RXF[u] = ldv<VX>(RFB, lo_xq, u * 64 * (int)sizeof(VX));
         if (MODE == M2_SECOND) RC[u] = ldv<VR>(RCB, lo_xc, u * 64 * (int)sizeof(VR));
@@ -525,13 +541,38 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
                             : pow2_floor(min_c(PAIRS, 32 / (SP * NR * (int)(sizeof(T) / 4))));
     static_assert(MB >= 1 && PAIRS % MB == 0 && (!PIPE || MB * NB == PAIRS),
                   "write-out batches must tile the pairs exactly");
-    const int t_wo = p * 64 + lane;
+    // Pair i of a thread: lane ln = (i*P + p)*8 + lane/8, step cc = lane%8 of
+    // the chunk. Its plane index comes in 1D/2D from the step's record, which
+    // the steps leave in LDS. In 3D it is a constant of the thread plus the
+    // part of the period (period_bases), of the two a pair's threads are in:
+    // ch - (i*P + p), or the one before it where cc < lane/8; and no record is
+    // loaded: the chunk's memory instructions are what bounds the 3D sweep
+    // (92x90x69 domain: FP32 2744 -> 2266 us a sweep, FP64 6400 -> 6022; the
+    // smallest, a 37x29x23 box in FP64, 148.5 -> 150.2). In 2D the column and
+    // strip of a thread take more arithmetic than the records cost (FP64
+    // 193x131 masked section 144 -> 181 us, FP32 256^2 square 78.6 -> 76.2).
+    const int cc = lane & 7, l8 = lane >> 3;
+    const int row_i = kC2 * P * NR;         // rows from a pair to the thread's next
+    const int row_t = (p * kC2 + l8) * NR;  // row of the thread's first pair
+    const int colp = (cc - l8) & 7;         // thread's column in its block
+    const bool before = cc < l8;
+    int pi_t = 0, n_row = 0;                // plane index of the thread's first pair, less the period's part
+    if constexpr (L3) {
+      const bool flipx = (o >> ax0) & 1, flipr = (o >> ax1) & 1;
+      const int n_col = ax0 == 0 ? nx : (ax0 == 1 ? ny : I.nz);
+      n_row = ax1 == 0 ? nx : (ax1 == 1 ? ny : I.nz);
+      const int x = flipx ? n_col - 1 - colp : colp;
+      pi_t = (x >> 3) * I.part_bs + (x & 7) * I.part_cs + row_t * dy - (flipr ? (n_row - 1) * dy : 0);
+    }
+    const CAS int2* PER = L3 ? cp(I.per_base) + (size_t)o * I.per_stride : nullptr;
+    int2 wper[MB][2];
     // steps after which batch b is read from LDS and, some steps later (an LDS
     // read of 16 bytes per lane by every wave takes about two steps), stored:
     // one batch after steps 0 and 3, two after 0, 3 and 6, four after 0, 2, 4,
     // 6 and 7
     auto wo_at = [](int b) constexpr { return NB == 4 ? 2 * b : 3 * b; };
     auto wo_gap = [](int b) constexpr { return NB == 4 ? (b == 3 ? 1 : 2) : 3; };
+    int wpb = 0;   // first pair of the batch in wraw
     int wvv[MB];
     // the constants of the P waves' ordinates: in registers while there are
     // few, else one per lane of a register and taken with readlane
@@ -564,11 +605,16 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
     auto wo_read = [&](int b, int chw) BTE_INL {
       const int bw = chw & 1;
       const int* scr = scid + (bw * R + r) * kC2 * CS;
+      wpb = b * MB;
 #pragma unroll
       for (int mi = 0; mi < MB; ++mi) {
-        const int e = (b * MB + mi) * (P * 64) + t_wo;
-        const int ln = e >> 3, cc = e & 7;
-        wvv[mi] = scr[cc * CS + ln];
+        const int ln = ((b * MB + mi) * P + p) * 8 + l8;
+        if constexpr (!L3) wvv[mi] = scr[cc * CS + ln];
+        if constexpr (L3) {
+          const int q = chw - ((b * MB + mi) * P + p) + kPerPad;
+          wper[mi][0] = PER[q];
+          wper[mi][1] = PER[q - 1];
+        }
 #pragma unroll
         for (int a = 0; a < SP; ++a) {
           const T* sp = stage + (size_t)(PIPE ? bw : a) * plane_sz + (size_t)r * kC2 * RS + cc * RS + ln * NR;
@@ -588,8 +634,17 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
     auto wo_store = [&](bool on) BTE_INL {
 #pragma unroll
       for (int mi = 0; mi < MB; ++mi) {
-        const int v = on ? wvv[mi] : -1;
-        const int cid0 = v >> 5;
+        const int i = wpb + mi;
+        int cid0;
+        bool ok;
+        if constexpr (L3) {
+          ok = on && colp < (before ? wper[mi][1].y : wper[mi][0].y);
+          cid0 = (before ? wper[mi][1].x : wper[mi][0].x) + pi_t + i * row_i * dy;
+        } else {
+          const int v = on ? wvv[mi] : -1;
+          ok = v >= 0;
+          cid0 = v >> 5;
+        }
 #pragma unroll
         for (int a = 0; a < NACC; ++a) {
           VR sm = wraw[PS ? 0 : a][mi][0];
@@ -611,15 +666,15 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
             // rows, or past either end of the plane, where the buffer's range
             // check drops it
 #pragma unroll
-            for (int k = 0; k < NR; ++k) bst(sm[k], PRS[a], v >= 0 ? (cid0 + k * dy) * (int)sizeof(T) : kOOB);
+            for (int k = 0; k < NR; ++k) bst(sm[k], PRS[a], ok ? (cid0 + k * dy) * (int)sizeof(T) : kOOB);
           } else {
             // 3D: planes have no padding rows, the index of a row past the
             // grid's end is a cell of the next line: rows outside the grid
-            // (record bit k clear) are not stored
+            // are not stored
 #pragma unroll
             for (int k = 0; k < NR; ++k) {
               const int c = cid0 + k * dy;
-              int off = (v >= 0 && ((v >> k) & 1)) ? (c + __mul24(c >> 8, pgap)) * (int)sizeof(T) : kOOB;
+              int off = ok && row_t + i * row_i + k < n_row ? (c + __mul24(c >> 8, pgap)) * (int)sizeof(T) : kOOB;
               // (opaque, so that the store stays one instruction rather than
               // being split into a branch per case of the select)
               asm volatile("" : "+v"(off));
@@ -704,6 +759,16 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
       int* scw = scid + (bufi * R + r) * kC2 * CS;
       int out_cnt = 0;
       in_rows = max(max(cfl_next, cfl_2), cfl_3) >> 8;
+      // a chunk that reads its flags reloads each after its step; before the
+      // first of a run of such chunks they are loaded here
+      constexpr bool FLAGS = !RECS && (IN != 0 || XS || OUT);
+      if constexpr (!RECS && !FLAGS)
+        if ((cfl_next & 0xFF) != 0) load_flags(ch + 1);
+      // a step's record, or its flags
+      auto rec_of = [&](auto u) BTE_INL {
+        if constexpr (RECS) return RR[u % KD];
+        else return make_int2(0, FR[u]);
+      };
       // the chunk's prefetch: 3D through the fixed views with a uniform offset
       // (fewer scalar registers live), 1D/2D through views based at the first
       // position prefetched in the chunk (immediate offsets per step)
@@ -727,7 +792,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
 #pragma unroll
         for (int k = 0; k < NR; ++k) dst[k] = ip[k];
       };
-      if constexpr (XS) read_xv(RR[0], xv[0]);
+      if constexpr (XS) read_xv(rec_of(std::integral_constant<int, 0>()), xv[0]);
       // 3D: a lane's stream entries (rows ascending, then the step, lane and
       // plane axes, from its offset), for the step of record rn. The offset
       // of an axis without an inflow may point up to six entries past the
@@ -748,16 +813,17 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
           pin[k][2] = inbuf[ez];
         }
       };
-      if constexpr (L3 && IN == 2) in_read(RR[0]);
+      if constexpr (L3 && IN == 2) in_read(rec_of(std::integral_constant<int, 0>()));
 
       auto step = [&](auto u_tag) BTE_INL {
         constexpr int u = decltype(u_tag)::value;
         constexpr int sl = u % KD;
-        const int2 rec = RR[sl];
+        constexpr std::integral_constant<int, (u + 1) % kC2> next_step{};
+        const int2 rec = rec_of(u_tag);
         // both halves of the record stay live until here, whatever the body
         // uses: a half the body ignores would otherwise free its register
         // while the load is in flight, and reusing it waits for that load
-        asm volatile("" ::"v"(rec.x), "v"(rec.y));
+        if constexpr (RECS) asm volatile("" ::"v"(rec.x), "v"(rec.y));
         const VX xq = RX[sl];
         VX xf;
         if (MODE == M2_TAUGRAD) xf = RXF[sl];
@@ -805,7 +871,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
           for (int k = 0; k < NR; ++k)
 #pragma unroll
             for (int g = 0; g < G; ++g) f[g][k] = xs ? xv[u & 1][k] * den[g] : f[g][k];
-          if (u + 1 < kC2) read_xv(RR[(u + 1) % KD], xv[(u + 1) & 1]);
+          if (u + 1 < kC2) read_xv(rec_of(next_step), xv[(u + 1) & 1]);
         }
 
         constexpr unsigned kInAll = rowmask(B_INX | B_INY | B_INZ, NR, RB);
@@ -842,7 +908,7 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
             f[0][k] = fn;
             zc[0] = fn;
           }
-          if (u + 1 < kC2) in_read(RR[(u + 1) % KD]);
+          if (u + 1 < kC2) in_read(rec_of(next_step));
         } else if (IN == 2 && __ballot(fl & kInAll) != 0ull) {
           // entries of this lane: rows ascending, then the step, lane and
           // plane axes, from its offset
@@ -906,8 +972,6 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
           }
           *reinterpret_cast<VR*>(stg0 + (size_t)(PIPE ? 0 : a) * plane_sz + u * RS + lane * NR) = acc;
         }
-        scw[u * CS + lane] = rec.x;  // every wave of the slot writes the same records
-
         // ---- the strip's top row for the next slot (lane 63), when a strip
         //      follows at all
         if (ring_w) {
@@ -977,6 +1041,9 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
             }
         }
 
+        // every wave of the slot writes the same records
+        if constexpr (!L3) scw[u * CS + lane] = rec.x;
+
         // ---- the previous chunk's write-out
         if constexpr (PIPE) {
           auto batch = [&](auto b) BTE_INL {
@@ -1009,7 +1076,8 @@ __global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
         //      fence keeps the loads after the last use of the old values, so
         //      every slot is reloaded in place
         __builtin_amdgcn_sched_barrier(0);
-        RR[sl] = ldrec_b(rr, lo_rec, (sb + u * 64) * 8);
+        if constexpr (RECS) RR[sl] = ldrec_b(rr, lo_rec, (sb + u * 64) * 8);
+        if constexpr (FLAGS) FR[u] = bld<int>(RRB, lo_rec + ((ch + 1) * kC2 + u) * 512 + 4);
         RX[sl] = ldv<VX>(rx, lo_xq, (sb + u * 64) * (int)sizeof(VX));
         if (MODE == M2_TAUGRAD) RXF[sl] = ldv<VX>(rf, lo_xq, (sb + u * 64) * (int)sizeof(VX));
         if (MODE == M2_SECOND) RC[sl] = ldv<VR>(rc, lo_xc, (sb + u * 64) * (int)sizeof(VR));

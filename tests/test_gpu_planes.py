@@ -62,6 +62,18 @@ def test_planes_3d(hip_lib, precision, P, n, kind):
     check(hip_lib, p, precision, dict(P=P, NR=1))
 
 
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n,NR,P,kind", [((1, 9, 8), 1, 8, 1), ((9, 1, 17), 2, 4, 1), ((17, 16, 1), 2, 2, 2),
+                                         ((100, 9, 7), 2, 8, 1), ((7, 126, 3), 2, 1, 1), ((64, 65, 2), 2, 4, 2)])
+def test_period_indices_3d(hip_lib, precision, n, NR, P, kind):
+    """Plane indices formed from the period table, and chunks whose boundary
+    entries fill no, one or several rows of 64: thin boxes (one period of a
+    block, blocks of one column), lanes of one and two rows, axes of each role
+    run both ways."""
+    p = bi.random_box_3d(*n, seed=4, n_bands=2, n_theta=2, n_phi=1, kinds=(0, kind))
+    check(hip_lib, p, precision, dict(P=P, NR=NR))
+
+
 @pytest.mark.parametrize("make", [lambda: bi.square_2d(19, L=0.1e-6, n_bands=3, n_theta=2, n_phi=2),
                                   lambda: bi.random_box_2d(13, 9, seed=3, n_bands=2, n_theta=1, n_phi=1),
                                   lambda: bi.random_box_3d(9, 5, 6, seed=5, n_bands=2, n_theta=1, n_phi=1)],
