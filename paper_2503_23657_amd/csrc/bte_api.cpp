@@ -816,7 +816,7 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
       }
       film.push_back(f);
     }
-    ok = ok && film_lds_bytes((long long)es, film_cpl(h->film_cells), n_grp_inst) <= kFilmLds;
+    ok = ok && film_lds_bytes(film_cpl(h->film_cells), n_grp_inst) <= kFilmLds;
     if (ok) HIPCHK(pp.upload(&h->d_film, film));
   }
   // LDS carve-up

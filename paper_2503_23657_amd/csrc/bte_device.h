@@ -412,8 +412,8 @@ constexpr int kFilmCells = 1024;        // longest film: 16 cells per lane
 // waves: their state needs more than the 128 registers sixteen waves leave
 __host__ __device__ constexpr int film_cpl(int n) { return n <= 64 ? 1 : n <= 128 ? 2 : n <= 256 ? 4 : n <= 512 ? 8 : 16; }
 __host__ __device__ constexpr int film_waves(int cpl) { return cpl == 16 ? 8 : 16; }
-__host__ __device__ constexpr long long film_lds_bytes(long long es, int cpl, int n_grp) {
-  return 8ll * 64 * (film_waves(cpl) * (cpl < 4 ? 4 : cpl) + cpl) + n_grp * (kFilmConst + 1) * es;
+__host__ __device__ constexpr long long film_lds_bytes(int cpl, int n_grp) {
+  return 8ll * 64 * (film_waves(cpl) * (cpl < 4 ? 4 : cpl) + cpl) + n_grp * (kFilmConst + 1) * 8ll;
 }
 
 struct UbfInitArgs {

@@ -12,6 +12,11 @@
 // composes their affine maps, and a scan over the wave's lanes (DPP within
 // rows of 16, then row broadcasts) gives each lane the value entering its
 // cells: the chain is CPL + 6 + CPL steps long instead of the film's length.
+// The arithmetic is double for both precisions (T is that of the constants and
+// the stored state): a scan rounds in another order than the cell-by-cell walk,
+// and dJ/dtau, whose terms nearly cancel, showed it in single precision (errors
+// up to 1.1e-5 where the walk's was 1.5e-6; now as the walk's). A film is bound
+// by latency, not by the rate of its arithmetic.
 // Half of the waves sweep rightward, half leftward; a wave adds the sums of its
 // ordinates in double registers, the waves' sums meet in LDS.
 //
@@ -30,10 +35,6 @@ namespace {
 
 // the value of the lane CTRL names (rows of ROWS only), `old` elsewhere
 template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp(float old, float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, ROWS, 0xF, false));
-}
-template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp(double old, double v) {
   const long long o = __double_as_longlong(old), x = __double_as_longlong(v);
   const int lo = __builtin_amdgcn_update_dpp((int)o, (int)x, CTRL, ROWS, 0xF, false);
@@ -42,9 +43,9 @@ __device__ __forceinline__ double dpp(double old, double v) {
 }
 
 // the maps f -> A f + B of earlier lanes composed into this lane's
-template <int CTRL, int ROWS, typename T>
-__device__ __forceinline__ void compose(T& A, T& B) {
-  const T a = dpp<CTRL, ROWS>(T(1), A), b = dpp<CTRL, ROWS>(T(0), B);
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void compose(double& A, double& B) {
+  const double a = dpp<CTRL, ROWS>(1.0, A), b = dpp<CTRL, ROWS>(0.0, B);
   B = fma(A, b, B);
   A *= a;
 }
@@ -58,8 +59,8 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
   extern __shared__ __align__(16) char lds[];
   double* sA = reinterpret_cast<double*>(lds);        // [NW][N] the waves' sums; the residual reduction
   double* sX = sA + NW * 64 * (CPL < 4 ? 4 : CPL);    // [N] Delta T or lambda
-  T* sC = reinterpret_cast<T*>(sX + N);               // [n_grp][kFilmConst] group constants, sweep inflow
-  T* sO = sC + (size_t)A.n_grp * kFilmConst;                // [n_grp] outflow at a reflecting wall
+  double* sC = sX + N;                                // [n_grp][kFilmConst] group constants, sweep inflow
+  double* sO = sC + (size_t)A.n_grp * kFilmConst;                // [n_grp] outflow at a reflecting wall
   const int inst = blockIdx.x;
   const InstDev& I = A.inst[inst];
   const FinInst& F = A.fin[inst];
@@ -79,23 +80,23 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
   for (int g = tid; g < A.n_grp; g += NT) {
     const int4 gi = A.grp_i[(size_t)inst * A.n_grp + g];
     const T* r = reinterpret_cast<const T*>(A.grp_t) + ((size_t)inst * A.n_grp + g) * grp_stride(1);
-    T* c = sC + (size_t)g * kFilmConst;
+    double* c = sC + (size_t)g * kFilmConst;
     c[FC_KS] = r[0];
     c[FC_CQ] = r[1];
     c[FC_A] = r[go_a(1, 0)];
     c[FC_DEN] = r[go_den(1)];
-    c[FC_IN] = r[go_den(1)] * ubf[(size_t)gi.w * I.n_bface + W.slot[gi.y & 1]];
+    c[FC_IN] = (double)r[go_den(1)] * (double)ubf[(size_t)gi.w * I.n_bface + W.slot[gi.y & 1]];
     c[FC_W0] = r[go_wacc(1, 0)];
     c[FC_W1] = r[go_wacc(1, 1)];
     c[FC_WO] = r[go_wo(1, 0)];
   }
-  T q[CPL];  // the source of the lane's cells, in sweep order (cell i or n - 1 - i)
+  double q[CPL];  // the source of the lane's cells, in sweep order (cell i or n - 1 - i)
 #pragma unroll
   for (int j = 0; j < CPL; ++j) {
     const int i = lane * CPL + j, c = oct ? n - 1 - i : i;
     q[j] = i < n ? reinterpret_cast<const T*>(I.xq[cur])[2 * ((size_t)oct * I.pos_per_oct +
                                                               I.pos[(size_t)oct * I.n_part + plane_index(c)]) + 1]
-                 : T(0);
+                 : 0.0;
   }
   double qm[CT], res[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -122,19 +123,19 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
   for (int it = 0; it < A.n_iter; ++it) {
     const bool last = it == A.n_iter - 1;
     const bool withq = !adj && it >= A.n_iter - 2;
-    T x[CPL];
+    double x[CPL];
     double acc[CPL], acq[CPL];
 #pragma unroll
     for (int j = 0; j < CPL; ++j) {
       const int i = lane * CPL + j, c = oct ? n - 1 - i : i;
-      x[j] = i < n ? (T)sX[c] : T(0);
+      x[j] = i < n ? sX[c] : 0.0;
       acc[j] = acq[j] = 0.0;
     }
     for (int g = g0 + wave % HW; g < g1; g += HW) {
-      const T* c = sC + (size_t)g * kFilmConst;
-      const T kS = c[FC_KS], cQ = c[FC_CQ], a = c[FC_A], fin = c[FC_IN];
-      const double w0 = (double)c[FC_W0], w1 = (double)c[FC_W1];
-      T Am = T(1), Bm = T(0);
+      const double* c = sC + (size_t)g * kFilmConst;
+      const double kS = c[FC_KS], cQ = c[FC_CQ], a = c[FC_A], fin = c[FC_IN];
+      const double w0 = c[FC_W0], w1 = c[FC_W1];
+      double Am = 1.0, Bm = 0.0;
 #pragma unroll
       for (int j = 0; j < CPL; ++j) {
         Bm = fma(a, Bm, fma(kS, x[j], cQ * q[j]));
@@ -146,13 +147,13 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
       compose<0x118, 0xF>(Am, Bm);
       compose<0x142, 0xA>(Am, Bm);  // row_bcast:15 into rows 1 and 3
       compose<0x143, 0xC>(Am, Bm);  // row_bcast:31 into rows 2 and 3
-      T f = fma(dpp<0x138, 0xF>(T(1), Am), fin, dpp<0x138, 0xF>(T(0), Bm));  // wave_shr:1
-      T fo = T(0);
+      double f = fma(dpp<0x138, 0xF>(1.0, Am), fin, dpp<0x138, 0xF>(0.0, Bm));  // wave_shr:1
+      double fo = 0.0;
 #pragma unroll
       for (int j = 0; j < CPL; ++j) {
         f = fma(a, f, fma(kS, x[j], cQ * q[j]));
-        acc[j] = fma(w0, (double)f, acc[j]);
-        if (withq) acq[j] = fma(w1, (double)f, acq[j]);
+        acc[j] = fma(w0, f, acc[j]);
+        if (withq) acq[j] = fma(w1, f, acq[j]);
         fo = j == jo ? f : fo;
       }
       if (reflect && lane == lo) sO[g] = c[FC_WO] * fo;
@@ -180,20 +181,20 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
         // (the end an ordinate of this octant enters through)
         const int face = gi.y & 1, kind = W.kind[face];
         if (kind == BTE_BC_ISOTHERMAL) continue;
-        T u;
+        double u;
         if (kind == BTE_BC_SPECULAR) {
           const int a = gi.w - gi.x * A.rows;
           const int2 src = A.src[face * A.rows + a];
           if (src.x < 0) continue;
-          u = (T)((double)sO[A.grp_ob[src.x * A.B + gi.x].x + src.y] * A.inv_wq[face * A.rows + a]);
+          u = sO[A.grp_ob[src.x * A.B + gi.x].x + src.y] * A.inv_wq[face * A.rows + a];
         } else {
           const int2 gr = A.grp_ob[(1 - face) * A.B + gi.x];
           double s = 0.0;
-          for (int k = 0; k < gr.y; ++k) s += (double)sO[gr.x + k];
-          u = (T)(s * W.inv_half[face]);
+          for (int k = 0; k < gr.y; ++k) s += sO[gr.x + k];
+          u = s * W.inv_half[face];
         }
         sC[(size_t)g * kFilmConst + FC_IN] = sC[(size_t)g * kFilmConst + FC_DEN] * u;
-        if (last) ubf[(size_t)gi.w * I.n_bface + W.slot[face]] = u;
+        if (last) ubf[(size_t)gi.w * I.n_bface + W.slot[face]] = (T)u;
       }
     }
     __syncthreads();
@@ -260,7 +261,7 @@ template <typename T, int CPL, int NW>
 hipError_t film_one(const FilmArgs& a, int n_inst, hipStream_t st) {
   auto k = film_chunk_kernel<T, CPL, NW>;
   static_assert(NW == film_waves(CPL), "the LDS a launch asks for");
-  const size_t lds = film_lds_bytes(sizeof(T), CPL, a.n_grp);
+  const size_t lds = film_lds_bytes(CPL, a.n_grp);
   static const hipError_t attr = hipFuncSetAttribute(
       reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kFilmLds);
   if (attr != hipSuccess || lds > (size_t)kFilmLds) return hipErrorInvalidValue;
