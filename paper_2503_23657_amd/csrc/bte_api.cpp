@@ -188,6 +188,8 @@ struct bte_ctx {
   double t0 = 1e-12;
   Plan plan;
   bool plan_set = false;
+  bool auto_plan = false;              // the plan is default_plan's (none was set, tuned or read from a cache)
+  Plan base_plan;                      // what a plan given in part is completed from while it is
   std::vector<Inst> inst;
   bool has_diffuse = false;
   bool has_specular = false;
@@ -211,6 +213,7 @@ struct bte_ctx {
   long long part_extra = 0, store_extra = 0;  // bytes that order adds to need_plan and need_store
   GroupSet gs;                         // ordinate groups of the current plan
   Plan sched_plan;                     // plan the host schedules were built for
+  int sched_nr = 0;                    // its NR as asked for
   bool sched_valid = false;
   int order = 1;                       // face reconstruction: 1 first order, 2 second order (deferred correction)
   bool l3r = false;                    // 3D problem swept by the rows-per-lane kernel (else the pencil-block one)
@@ -442,11 +445,16 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
   DevPool& pp = *h->ppool;
   const int prec = h->precision;
   const size_t es = elem(prec);
-  const bool reuse_sched = h->sched_valid && h->sched_plan.G == pl.G && h->sched_plan.R == pl.R &&
-                           h->sched_plan.P == pl.P && h->sched_plan.C == pl.C && h->sched_plan.NR == pl.NR;
+  // (a schedule knows nothing of the groups; in the 3D rows layout the NR asked
+  // for may have been raised)
+  const bool reuse_groups = h->sched_valid && h->sched_plan.G == pl.G && h->sched_plan.P == pl.P;
+  const bool reuse_sched = h->sched_valid && h->l3r == R3 && h->sched_plan.R == pl.R && h->sched_plan.C == pl.C &&
+                           (h->sched_plan.NR == pl.NR || (R3 && h->sched_nr == pl.NR));
   h->sched_valid = false;
-  if (!reuse_sched) h->gs = build_groups(h->ords, h->B, h->dim, pl.G, pl.P);
+  if (!reuse_groups) h->gs = build_groups(h->ords, h->B, h->dim, pl.G, pl.P);
   const GroupSet& gs = h->gs;
+  if (!reuse_sched) h->sched_nr = pl.NR;
+  else if (R3) pl.NR = h->sched_plan.NR;
   if (R3 && !reuse_sched) {
     // rows-per-lane schedules of every instance, with one NR for all (the
     // kernel's shape): the largest any instance needs
@@ -495,7 +503,7 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
       return BTE_ERR_INVALID;
     }
     const Schedule& S = I.sch;
-    if (!reuse_sched) I.ctab_made = false;
+    if (!reuse_sched || !reuse_groups) I.ctab_made = false;
     if (h->has_specular) {
       // every mirror ordinate must find its outflow entry at each specular face
       const int nbf = (int)I.hi.bf_cell.size();
@@ -994,6 +1002,80 @@ bte_status build_plan_impl(bte_ctx* h, const Plan& pl) {
   return s;
 }
 
+// The plan a new handle had before its shape is looked at: in 3D the
+// rows-per-lane layout, P waves of one octant per workgroup; in 1D/2D one strip
+// of 64*NR rows, which covers ny <= 256.
+Plan basic_plan(const bte_ctx* h) {
+  Plan pl;
+  pl.G = 1;
+  pl.R = 1;
+  pl.C = kC2;
+  if (h->dim == 3) {
+    pl.P = h->precision == BTE_PREC_FP32 ? 8 : 4;
+    pl.NR = 1;
+  } else {
+    int ny = 1;
+    for (auto& I : h->inst) ny = std::max(ny, I.hi.n[1]);
+    pl.NR = ny <= 64 ? 1 : ny <= 128 ? 2 : 4;
+    pl.P = h->precision == BTE_PREC_FP32 ? 4 : 2;
+  }
+  return pl;
+}
+
+// The plan of a handle that none was given to, by the groups (bands times
+// ordinates, of all instances) against the 256 CUs. Times of one iteration in
+// us, the basic plan's and this one's:
+//   2D, ny <= 128, FP64: four waves share a plane instead of two. 64^2, 160
+//     groups 40.8 -> 39.4, 960 groups 66.0 -> 53.2; 128^2, 960 groups
+//     88.3 -> 73.4; a masked 60x100, 480 groups 86.0 -> 80.6; second-order
+//     128^2, 960 groups 277 -> 230 (64^2, 160 groups 59.6 -> 60.2).
+//   2D, 128 < ny <= 256, first order (second-order sweeps march along single
+//     strips of four rows per lane):
+//     walls inside or reflecting ones: most chunks then have boundary entries,
+//       whose work is per row of a lane, and two slots of two rows take fewer
+//       steps' time than one of four while each workgroup of four waves has a
+//       CU (up to 512 groups). Masked 193x131, 480 groups: FP64 178 -> 158, FP32
+//       162 -> 143; 240x250: 241 -> 220, 202 -> 178; a rectangle of 240x250 with
+//       diffuse walls, 160 groups: 196 -> 175, 179 -> 158; at 960 groups it is
+//       slower (FP64 326 -> 389, FP32 192 -> 204).
+//     FP64 else, more groups than CUs: two rows per lane in one slot, four
+//       waves to a plane. 256^2, 480 groups 161 -> 153, 960 groups 302 -> 190;
+//       160 groups: 106 -> over 114.
+//   3D: FP32 with no more groups than CUs: 4 waves share a plane instead of 8.
+//     37x29x23, 160 groups 181 -> 176, 60x60x50, 256 groups 639 -> 628; 46x45x35,
+//     512 groups 552 -> 561. FP64 with more than four groups per CU: 8 instead
+//     of 4. 46x45x35, 1920 groups 1197 -> 1018; 23x23x18, 960 groups 211 -> 225.
+Plan default_plan(const bte_ctx* h, int order) {
+  Plan pl = basic_plan(h);
+  const long long n = (long long)h->B * (long long)h->ords.size() * (long long)h->inst.size(), cu = h->n_cu;
+  const bool f64 = h->precision != BTE_PREC_FP32;
+  if (h->dim == 3) {
+    if (!f64 && n <= cu) pl.P = 4;
+    if (f64 && n > 4 * cu) pl.P = 8;
+  } else if (h->dim == 2) {
+    int lo = 1 << 30, hi = 0;
+    bool walls = h->has_diffuse || h->has_specular;
+    for (auto& I : h->inst) {
+      lo = std::min(lo, I.hi.n[1]);
+      hi = std::max(hi, I.hi.n[1]);
+      walls = walls || I.hi.n_active < I.hi.ncell;
+    }
+    if (hi <= 128) {
+      pl.P = 4;
+    } else if (order == 1 && lo > 128 && hi <= 256) {
+      if (walls && n <= 2 * cu) {
+        pl.NR = 2;
+        pl.R = 2;
+        pl.P = 2;
+      } else if (f64 && n > cu) {
+        pl.NR = 2;
+        pl.P = 4;
+      }
+    }
+  }
+  return pl;
+}
+
 // (Re)build the plan-dependent state. With a bound workspace the plan's bytes
 // are counted first, and a plan that does not fit is rejected before any array
 // of the current plan is overwritten.
@@ -1012,6 +1094,29 @@ bte_status build_plan(bte_ctx* h, const Plan& pl) {
     return build_plan_impl(h, Plan(h->plan));
   }
   return build_plan_impl(h, pl);
+}
+
+// The default plan of the handle's order, or the base plan where only that one
+// stays within the allocation-free solve's fixed array.
+bte_status build_default_plan(bte_ctx* h) {
+  const Plan base = h->base_plan, pl = default_plan(h, h->order);
+  bte_status s = build_plan(h, pl);
+  if (s != BTE_OK || (pl.R == base.R && pl.P == base.P && pl.NR == base.NR)) return s;
+  const size_t need = h->need_static + h->need_plan, with = need + h->need_store;
+  if (with <= kStaticScratchBytes) return s;
+  // (the base plan's planes and field alone tell for most, before it is built)
+  size_t planes = 0, field = 0;
+  const size_t es = h->precision == BTE_PREC_FP32 ? 4 : 8, n_grp = (size_t)h->B * h->ords.size();
+  for (auto& I : h->inst) {
+    planes += h->nacc_max * (n_grp / base.P) * I.hi.ncell * es;
+    field += n_grp * I.hi.ncell * es;
+  }
+  const size_t least = h->need_static + planes;
+  if ((need <= kStaticScratchBytes || least > kStaticScratchBytes) && least + field > kStaticScratchBytes) return s;
+  s = build_plan(h, base);
+  const size_t need0 = h->need_static + h->need_plan, with0 = need0 + h->need_store;
+  if (s == BTE_OK && ((need > kStaticScratchBytes && need0 <= kStaticScratchBytes) || with0 <= kStaticScratchBytes)) return s;
+  return build_plan(h, pl);
 }
 
 // Plan-independent per-instance device data.
@@ -1217,27 +1322,11 @@ bte_status create_common(int n_inst, const bte_geometry* geoms, const bte_bands*
   h->pool_mode = DevPool::COUNT;
   bte_status s = build_static(h.get());
   if (s != BTE_OK) return s;
-  Plan pl;
-  if (h->dim == 3) {
-    // the rows-per-lane layout, P waves of one octant per workgroup (fewer
-    // when the LDS does not fit); the pencil blocks when the problem does not
-    // fit the rows-per-lane layout
-    pl.G = 1;
-    pl.R = 1;
-    pl.P = precision == BTE_PREC_FP32 ? 8 : 4;
-    pl.C = kC2;
-    pl.NR = 1;
-  } else {
-    // one strip of 64*NR rows covers ny <= 256; P waves share the partial sums
-    int ny = 1;
-    for (auto& I : h->inst) ny = std::max(ny, I.hi.n[1]);
-    pl.G = 1;
-    pl.R = 1;
-    pl.NR = ny <= 64 ? 1 : ny <= 128 ? 2 : 4;
-    pl.P = precision == BTE_PREC_FP32 ? 4 : 2;
-    pl.C = kC2;
-  }
-  s = build_plan(h.get(), pl);
+  Plan pl = basic_plan(h.get());
+  h->base_plan = pl;
+  s = build_default_plan(h.get());
+  const bool by_rule = s == BTE_OK;
+  if (!by_rule) s = build_plan(h.get(), pl);
   while (s != BTE_OK && h->dim == 3 && pl.NR >= 1 && pl.P > 1) {
     pl.P /= 2;
     s = build_plan(h.get(), pl);
@@ -1258,6 +1347,8 @@ bte_status create_common(int n_inst, const bte_geometry* geoms, const bte_bands*
     s = build_plan(h.get(), pl);
   }
   if (s != BTE_OK) return s;
+  if (!by_rule) h->base_plan = h->plan;
+  h->auto_plan = true;
   *out = h.release();
   return BTE_OK;
 }
@@ -1709,12 +1800,15 @@ bte_status apply_tune_cache(bte_ctx* h, const char* path, const double* d_Q, hip
   }
   if (found) {
     const Plan& c = h->plan;
+    const bool was_auto = h->auto_plan;
+    h->auto_plan = false;
     if (pl.G == c.G && pl.R == c.R && pl.P == c.P && pl.C == c.C && pl.NR == c.NR) return BTE_OK;
     const Plan old = h->plan;
     bte_status s = build_plan(h, pl);
     if (s != BTE_OK) {
       const std::string e = g_err;
       (void)build_plan(h, old);
+      h->auto_plan = was_auto;
       set_err("autotune cache %s: stored plan rejected: %s", path, e.c_str());
     }
     return s;
@@ -2031,7 +2125,12 @@ bte_status bte_set_order(bte_handle h, int order) {
   if (order == h->order) return BTE_OK;
   const int old_order = h->order;
   const Plan old = h->plan;
-  Plan p = h->plan;
+  if (h->auto_plan && h->plan.NR >= 1) {
+    h->order = order;
+    if (build_default_plan(h) == BTE_OK) return BTE_OK;
+    h->order = old_order;
+  }
+  Plan p = h->auto_plan ? h->base_plan : h->plan;
   if (order == 2) {
     p.G = 1;
     if (h->dim == 3 && p.NR < 1) {
@@ -2057,7 +2156,7 @@ bte_status bte_set_plan(bte_handle h, const bte_plan* plan) {
     set_err("null handle or plan");
     return BTE_ERR_INVALID;
   }
-  Plan p = h->plan;
+  Plan p = h->auto_plan ? h->base_plan : h->plan;
   if (plan->G) p.G = plan->G;
   if (plan->R) p.R = plan->R;
   if (plan->P) p.P = plan->P;
@@ -2069,6 +2168,8 @@ bte_status bte_set_plan(bte_handle h, const bte_plan* plan) {
     const std::string e = g_err;
     (void)build_plan(h, old);
     g_err = e;
+  } else {
+    h->auto_plan = false;
   }
   return s;
 }
@@ -2470,6 +2571,7 @@ bte_status autotune_impl(bte_ctx* h, const double* d_Q, int n_iters, hipStream_t
   (void)hipEventDestroy(e1);
   bte_status s = build_plan(h, bestp);
   if (s != BTE_OK) return s;
+  h->auto_plan = false;
   if (best) *best = bestp;
   return BTE_OK;
 }
