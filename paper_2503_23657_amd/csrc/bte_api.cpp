@@ -1041,6 +1041,13 @@ Plan basic_plan(const bte_ctx* h) {
 //     FP64 else, more groups than CUs: two rows per lane in one slot, four
 //       waves to a plane. 256^2, 480 groups 161 -> 153, 960 groups 302 -> 190;
 //       160 groups: 106 -> over 114.
+//   2D, first order, more than four groups per CU (batches): with several
+//     workgroups to a CU a step's time goes with its rows, so the rows per lane
+//     are those with the least steps times the measured cost of one (FP32 0.37 :
+//     0.53 : 1 for 1, 2 and 4 rows, FP64 0.28 : 0.52 : 1; four waves to a plane,
+//     which four rows in FP64 have no LDS for). Batches of squares of 33 to 159
+//     rows and columns: 64 in FP32 1406 -> 981, 8 in FP32 183 -> 131, 24 in FP64
+//     1082 -> 619.
 //   3D: FP32 with no more groups than CUs: 4 waves share a plane instead of 8.
 //     37x29x23, 160 groups 181 -> 176, 60x60x50, 256 groups 639 -> 628; 46x45x35,
 //     512 groups 552 -> 561. FP64 with more than four groups per CU: 8 instead
@@ -1060,7 +1067,19 @@ Plan default_plan(const bte_ctx* h, int order) {
       hi = std::max(hi, I.hi.n[1]);
       walls = walls || I.hi.n_active < I.hi.ncell;
     }
-    if (hi <= 128) {
+    if (order == 1 && n > 4 * cu) {
+      const double cost[2][3] = {{0.37, 0.53, 1.0}, {0.28, 0.52, 1.0}};  // of a step, by NR
+      double best = 0.0;
+      for (int i = 0; i < (f64 ? 2 : 3); ++i) {
+        double t = 0.0;
+        for (auto& I : h->inst) t += cost[f64][i] * schedule_steps_2d(I.hi.n[0], I.hi.n[1], 1 << i, 1);
+        if (i == 0 || t < best) {
+          best = t;
+          pl.NR = 1 << i;
+        }
+      }
+      pl.P = 4;
+    } else if (hi <= 128) {
       pl.P = 4;
     } else if (order == 1 && lo > 128 && hi <= 256) {
       if (walls && n <= 2 * cu) {

@@ -288,6 +288,26 @@ static int next_pow2(int x) {
   return p;
 }
 
+// Steps between the starts of consecutive strips: at least 63 + kC2 (the
+// previous strip's top row reaches the ring a chunk before it is read) and,
+// when a slot owns several strips, long enough for its strips not to overlap
+// (R*du >= V)
+static int strip_steps_2d(int V, int nS, int R) {
+  return nS > R ? std::max(63 + kC2, (V + R - 1) / R) : 63 + kC2;
+}
+
+// Steps of the 1D/2D schedule: the last strip ends when the last of its lanes
+// that hold rows does (the earlier ones' 64 lanes end before that: du > 63).
+// Steps for all 64 lanes of it cost a batch of 64 solves and adjoints of 33 to
+// 159 rows 218 instead of 192 ms, 24 iterations of a 193x131 section in FP64
+// 3.80 instead of 3.54 ms.
+int schedule_steps_2d(int nx, int ny, int NR, int R) {
+  const int H = 64 * NR, nS = (ny + H - 1) / H;
+  const int lanes = (ny - (nS - 1) * H + NR - 1) / NR;
+  const int T = (nS - 1) * strip_steps_2d(nx, nS, R) + nx + lanes - 1;
+  return (T + kC2 - 1) / kC2 * kC2;
+}
+
 // 1D/2D schedule of the rows-per-lane sweep. Lane l of wave slot r owns rows
 // 64*NR*s + NR*l + k (k < NR) of strip s and processes column i of it at clock
 // step t = s*du + l + i (strips r, r+R, ... belong to slot r). Positions of
@@ -305,17 +325,8 @@ static bool build_schedule_2d(const HostInst& hi, const Plan& plan, Schedule& s,
   const int H = 64 * NR;
   const int nS = (ny + H - 1) / H;
   const int V = nx;
-  // strips start du steps apart: at least 63 + C (the previous strip's top
-  // row reaches the ring a chunk before it is read) and, when a slot owns
-  // several strips, long enough for its strips not to overlap (R*du >= V)
-  const int du = nS > R ? std::max(63 + C, (V + R - 1) / R) : 63 + C;
-  // the last strip ends when the last of its lanes that hold rows does (the
-  // earlier ones' 64 lanes end before that: du > 63). Steps for all 64 lanes of
-  // it cost a batch of 64 solves and adjoints of 33 to 159 rows 218 instead of
-  // 192 ms, 24 iterations of a 193x131 section in FP64 3.80 instead of 3.54 ms.
-  const int lanes = (ny - (nS - 1) * H + NR - 1) / NR;
-  int T = (nS - 1) * du + V + lanes - 1;
-  T = (T + C - 1) / C * C;
+  const int du = strip_steps_2d(V, nS, R);
+  const int T = schedule_steps_2d(nx, ny, NR, R);
   const int Tp = T + kPad2;
   s.T = T;
   s.R = R;

@@ -113,6 +113,9 @@ void group_coefficients(const GroupSet& gs, const std::vector<Ordinate>& ords, c
                         const std::vector<double>& C, double t0, bool adjoint,
                         std::vector<double>& out);
 
+// steps of the 1D/2D rows-per-lane schedule
+int schedule_steps_2d(int nx, int ny, int NR, int R);
+
 // Sweep schedule of an instance. For 3D problems plan.NR = 0 selects the
 // pencil-block layout; NR >= 1 the rows-per-lane layout when the problem fits
 // it (a lane axis of at most 128 cells, at most 256 stream entries per chunk),

@@ -30,6 +30,8 @@ def shape(s):
     ("fp64", lambda: box(9, 257, 2, 1, 1), (1, 2, 4)), ("fp64", lambda: box(9, 129, 2, 1, 0), (1, 2, 4)),
     ("fp64", lambda: box(9, 131, 10, 4, 0), (1, 4, 2)), ("fp64", lambda: box(9, 131, 20, 4, 1), (1, 4, 2)),
     ("fp32", lambda: box(9, 131, 20, 4, 1), (1, 4, 4)),
+    ("fp32", lambda: box(150, 130, 20, 8, 0), (1, 4, 2)), ("fp32", lambda: box(60, 61, 20, 8, 0), (1, 4, 1)),
+    ("fp64", lambda: box(20, 130, 20, 8, 0), (1, 4, 1)),
     ("fp32", lambda: bi.random_box_3d(9, 7, 6, seed=1, n_bands=2, n_theta=1, n_phi=1), (1, 4, 1)),
     ("fp64", lambda: bi.random_box_3d(9, 7, 6, seed=1, n_bands=2, n_theta=1, n_phi=1), (1, 4, 1)),
 ])
