@@ -1087,9 +1087,12 @@ bool corr_tables(const HostInst& hi, const Schedule& s, int n_grp, CorrTables& o
     int nb = 0;
     for (int b : s.per_b) nb = std::max(nb, b + 1);
     out.tail = ((hi.n[ax[1]] + NR - 1) / NR + C - 1) / C;
-    // periods of a unit: a whole block, or at least twice the lanes' skew
+    // periods of a unit: a whole block, or at least the lanes' skew, which
+    // every unit walks beside its own periods (a 57x15x26 box with 160 groups
+    // in FP64: 270 us an iteration with at least twice the skew, 220 with the
+    // skew, 256 with one period; 68x22x59 in FP32: 638, 652, 650)
     const long long all = (long long)n_grp * s.n_per;
-    const int len = (int)std::max<long long>(all / kCorrWaves, 2 * out.tail);
+    const int len = (int)std::max<long long>(all / kCorrWaves, out.tail);
     std::vector<std::vector<int2>> units(s.n_oct);
     out.link.assign((size_t)s.n_oct * s.n_per, make_int2(0, 0));
     for (int o = 0; o < s.n_oct; ++o) {
