@@ -158,8 +158,14 @@ enum { M2_PLAIN = 0, M2_STORE = 1, M2_TAUGRAD = 2, M2_SECOND = 3 };
 // buffer of the wave (one load and one store per lane and chunk, the first
 // block's wall values prefilled); lane 0's lane-axis upwind value comes from
 // the wall table gpre.
+//
+// 3D workgroups have up to 8 waves, which leaves a wave 256 registers; with up
+// to four waves, FP64 with two rows per lane takes up to 512 instead of
+// spilling (92x90x69 domain 6061 -> 5575 us a sweep, 70x66x60 box 1089 -> 995).
+// With one row per lane two such workgroups on a CU are worth more than the few
+// spilled values (1920 groups: 278 us an iteration, 387 with 512 registers).
 template <typename T, int G, int NR, int P, int NACC, int MODE, bool L3 = false>
-__global__ void __launch_bounds__(L3 ? 512 : 256) sweep2d_kernel(SweepArgs A) {
+__global__ void __launch_bounds__(L3 && !(NR == 2 && P <= 4 && sizeof(T) == 8) ? 512 : 256) sweep2d_kernel(SweepArgs A) {
   using namespace s2d;
   static_assert(!L3 || (NR <= 2 && G == 1), "3D rows-per-lane: NR <= 2, one ordinate per lane");
   static_assert(MODE != M2_SECOND || G == 1, "second-order faces: one ordinate per lane");
