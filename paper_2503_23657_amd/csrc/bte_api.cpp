@@ -1028,19 +1028,23 @@ Plan basic_plan(const bte_ctx* h) {
 //   2D, ny <= 128, FP64: four waves share a plane instead of two. 64^2, 160
 //     groups 40.8 -> 39.4, 960 groups 66.0 -> 53.2; 128^2, 960 groups
 //     88.3 -> 73.4; a masked 60x100, 480 groups 86.0 -> 80.6; second-order
-//     128^2, 960 groups 277 -> 230 (64^2, 160 groups 59.6 -> 60.2).
+//     128^2, 960 groups 277 -> 230 (64^2, 160 groups 59.6 -> 60.2). Not below
+//     0.6 groups per CU (109x63 with specular walls, 80 groups 73.7 -> 76.6,
+//     144 groups 77.8 -> 78.8).
 //   2D, 128 < ny <= 256, first order (second-order sweeps march along single
 //     strips of four rows per lane):
 //     walls inside or reflecting ones: most chunks then have boundary entries,
-//       whose work is per row of a lane, and two slots of two rows take fewer
-//       steps' time than one of four while each workgroup of four waves has a
-//       CU (up to 512 groups). Masked 193x131, 480 groups: FP64 178 -> 158, FP32
+//       whose work is per row of a lane, and a step of two slots of two rows
+//       takes 0.72 of the time of one of four while each workgroup of four
+//       waves has a CU (up to 512 groups); narrow sections have too many more
+//       steps that way (52x246: 89 -> 93). Masked 193x131, 480 groups: FP64 178 -> 158, FP32
 //       162 -> 143; 240x250: 241 -> 220, 202 -> 178; a rectangle of 240x250 with
 //       diffuse walls, 160 groups: 196 -> 175, 179 -> 158; at 960 groups it is
 //       slower (FP64 326 -> 389, FP32 192 -> 204).
-//     FP64 else, more groups than CUs: two rows per lane in one slot, four
-//       waves to a plane. 256^2, 480 groups 161 -> 153, 960 groups 302 -> 190;
-//       160 groups: 106 -> over 114.
+//     FP64 else, more than two groups per CU: two rows per lane in one slot,
+//       four waves to a plane. 256^2, 960 groups 302 -> 190; at fewer it wins or
+//       loses with the size (256^2, 480 groups 161 -> 153, but the solve and
+//       adjoint of 183^2, 448 groups 23.0 -> 25.1 ms).
 //   2D, first order, more than four groups per CU (batches): with several
 //     workgroups to a CU a step's time goes with its rows, so the rows per lane
 //     are those with the least steps times the measured cost of one (FP32 0.37 :
@@ -1080,13 +1084,18 @@ Plan default_plan(const bte_ctx* h, int order) {
       }
       pl.P = 4;
     } else if (hi <= 128) {
-      pl.P = 4;
+      if (5 * n > 3 * cu) pl.P = 4;
     } else if (order == 1 && lo > 128 && hi <= 256) {
-      if (walls && n <= 2 * cu) {
+      double t1 = 0.0, t2 = 0.0;  // steps of one slot of four rows and of two slots of two
+      for (auto& I : h->inst) {
+        t1 += schedule_steps_2d(I.hi.n[0], I.hi.n[1], 4, 1);
+        t2 += schedule_steps_2d(I.hi.n[0], I.hi.n[1], 2, 2);
+      }
+      if (walls && n <= 2 * cu && 0.72 * t2 < t1) {
         pl.NR = 2;
         pl.R = 2;
         pl.P = 2;
-      } else if (f64 && n > cu) {
+      } else if (f64 && n > 2 * cu) {
         pl.NR = 2;
         pl.P = 4;
       }

@@ -25,11 +25,12 @@ def shape(s):
 
 
 @pytest.mark.parametrize("precision,p,want", [
-    ("fp64", lambda: box(9, 64, 2, 1, 0), (1, 4, 1)), ("fp64", lambda: box(9, 65, 2, 1, 1), (1, 4, 2)),
-    ("fp64", lambda: box(9, 129, 2, 1, 1, True), (2, 2, 2)), ("fp32", lambda: box(12, 256, 2, 1, 1), (2, 2, 2)),
+    ("fp64", lambda: box(9, 64, 5, 4, 0), (1, 4, 1)), ("fp64", lambda: box(9, 65, 5, 4, 1), (1, 4, 2)),
+    ("fp64", lambda: box(90, 129, 2, 1, 1, True), (2, 2, 2)), ("fp32", lambda: box(150, 256, 2, 1, 1), (2, 2, 2)),
     ("fp64", lambda: box(9, 257, 2, 1, 1), (1, 2, 4)), ("fp64", lambda: box(9, 129, 2, 1, 0), (1, 2, 4)),
-    ("fp64", lambda: box(9, 131, 10, 4, 0), (1, 4, 2)), ("fp64", lambda: box(9, 131, 20, 4, 1), (1, 4, 2)),
-    ("fp32", lambda: box(9, 131, 20, 4, 1), (1, 4, 4)),
+    ("fp64", lambda: box(9, 131, 10, 4, 0), (1, 2, 4)), ("fp64", lambda: box(9, 131, 17, 4, 0), (1, 4, 2)), ("fp64", lambda: box(9, 131, 20, 4, 1), (1, 4, 2)),
+    ("fp32", lambda: box(9, 131, 20, 4, 1), (1, 4, 4)), ("fp64", lambda: box(9, 131, 2, 1, 1), (1, 2, 4)),
+    ("fp64", lambda: box(9, 64, 2, 1, 0), (1, 2, 1)),
     ("fp32", lambda: box(150, 130, 20, 8, 0), (1, 4, 2)), ("fp32", lambda: box(60, 61, 20, 8, 0), (1, 4, 1)),
     ("fp64", lambda: box(20, 130, 20, 8, 0), (1, 4, 1)),
     ("fp32", lambda: bi.random_box_3d(9, 7, 6, seed=1, n_bands=2, n_theta=1, n_phi=1), (1, 4, 1)),
@@ -54,7 +55,7 @@ def test_partial_plan_and_order(hip_lib):
     """A plan given in part keeps the other fields of one strip of four rows
     per lane (two waves per slot would not fit beside four to a plane); the
     order picks its own default, and a plan that was given stays."""
-    p = box(20, 140, 2, 1, 1, True)
+    p = box(90, 140, 2, 1, 1, True)
     s = hip_lib.Solver(p, precision="fp32", plan=dict(P=4))
     assert shape(s) == (1, 4, 4)
     s.set_order(2)
