@@ -134,27 +134,34 @@ __global__ void __launch_bounds__(kFinThreads) finalize_kernel(FinArgs A, const 
   const T* part = reinterpret_cast<const T*>(I.part);
   const bool adj = (A.flags & FIN_ADJ) != 0, withq = (A.flags & FIN_Q) != 0;
   const int nq = withq ? (adj ? 1 : I.dim) : 0;
+  // the places of cell threadIdx.x % kFinCells in half of the octants' layouts
+  // (-1: no active cell), loaded ahead of the gather: one octant after the
+  // other behind it, load and store, they took longer (solves of a 64^2 square in
+  // FP64 3819 -> 3775 us, of the 37x29x23 box 4622 -> 4578, of the FP32 256^2
+  // square 9050 -> 9000)
+  static_assert(kFinThreads == 2 * kFinCells, "two threads per cell share the octants");
+  const int n_half = I.n_oct >> 1, o0 = cl < kFinCells ? 0 : n_half;
+  const int pcx = cbase + (cl & (kFinCells - 1));
+  int ps[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    ps[j] = j < n_half && pcx < I.n_part ? I.pos[(size_t)(o0 + j) * I.n_part + pcx] : -1;
+  const bool in_blk = c >= 0;
+  const bool act = in_blk && F.active[c];
+  const double old = act ? F.X[cur][c] : 0.0;
   // ---- per-cell totals of every needed plane (inactive cells' entries are
   //      gathered with their neighbours and dropped below)
   double tot[4];
   tot[0] = plane_total(part, I.n_jobs, I.part_jg, I.part_ld, I.n_part, cbase, slc);
   for (int d = 0; d < nq; ++d)
     tot[1 + d] = plane_total(part + (size_t)(1 + d) * plane, I.n_jobs, I.part_jg, I.part_ld, I.n_part, cbase, slc);
-  const bool in_blk = c >= 0;
-  const bool act = in_blk && F.active[c];
   double v[4] = {0.0, 0.0, 0.0, 0.0};  // sum dT^2, max |x|, sum d|q|^2, max |q| (+inf: non-finite)
   if (in_blk) {
     if (act) {
       double x = adj ? F.g[c] : 0.0;
       x += tot[0];
-      const double old = F.X[cur][c];
       F.X[nxt][c] = x;
-      // scatter into the skewed layouts of every octant
-      T* xq = reinterpret_cast<T*>(I.xq[nxt]);
-      for (int o = 0; o < I.n_oct; ++o) {
-        const int ps = I.pos[(size_t)o * I.n_part + pc];
-        xq[2 * ((size_t)o * I.pos_per_oct + ps)] = (T)x;
-      }
+      slc[0][cl] = x;
       bool bad = !isfinite(x);
       const double d = x - old;
       v[0] = d * d;
@@ -189,6 +196,12 @@ __global__ void __launch_bounds__(kFinThreads) finalize_kernel(FinArgs A, const 
       }
     }
   }
+  // ---- scatter into the skewed layouts of every octant
+  __syncthreads();
+  T* xq = reinterpret_cast<T*>(I.xq[nxt]);
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (ps[j] >= 0) xq[2 * ((size_t)(o0 + j) * I.pos_per_oct + ps[j])] = (T)slc[0][cl & (kFinCells - 1)];
   if (!(A.flags & FIN_CHECK)) {
     // no residual needed: only the iteration counter moves (last block);
     // non-finite values are caught at the next check. No block reads another
