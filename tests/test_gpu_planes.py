@@ -107,3 +107,11 @@ def test_gradient_across_plane_orders(hip_lib, make):
         qs[1][c] -= h
         fd = (J(p.replace(Q=qs[0])) - J(p.replace(Q=qs[1]))) / (2 * h)
         assert abs(fd - dq[c]) < 1e-5 * np.abs(dq).max(), (c, fd, dq[c])
+
+
+@pytest.mark.parametrize("n", [(6, 5, 7), (48, 40, 36)])
+def test_specular_update_bands(hip_lib, n):
+    """The specular walls' update with a thread per band (few faces) and with
+    all bands in a thread (512 workgroups of faces and ordinates and more)."""
+    p = bi.random_box_3d(*n, seed=1, n_bands=3, n_theta=2, n_phi=2, kinds=(0, bi.BC_SPECULAR))
+    check(hip_lib, p, "fp64", dict(P=4, NR=1))
