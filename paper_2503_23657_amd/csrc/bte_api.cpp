@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -206,10 +207,11 @@ struct bte_ctx {
   char* ws_base = nullptr;             // bound workspace
   size_t ws_cap = 0;
   bool ws_store = false;               // the bound workspace holds the adjoint's angular field
+  bool ws_lost = false;                // a workspace was bound, but its arrays could not be rebuilt
   size_t need_static = 0, need_plan = 0, need_store = 0;  // workspace bytes of the current plan
-  bool part_blocks = true;             // order of the cells in the partial-sum planes (see plane_order)
-  Plan part_plan;                      // plan and order it was chosen for (order 0: none yet)
-  int part_order = 0;
+  bool part_blocks = true;             // the build at hand orders the cells of its partial-sum planes in
+                                       // blocks of columns (see plane_order), else in grid order
+  std::map<std::array<int, 6>, bool> part_choice;  // that choice of every plan built so far (see plan_key)
   long long part_extra = 0, store_extra = 0;  // bytes that order adds to need_plan and need_store
   GroupSet gs;                         // ordinate groups of the current plan
   Plan sched_plan;                     // plan the host schedules were built for
@@ -979,26 +981,31 @@ bte_status finish_plan(bte_ctx* h, const Plan& pl, DevPool& pp) {
 // Device workspace of bte_solve_noalloc (below): the largest need it accepts.
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 
+// What the choice of the planes' order depends on, beside the problem.
+std::array<int, 6> plan_key(const bte_ctx* h, const Plan& pl) { return {h->order, pl.G, pl.R, pl.P, pl.C, pl.NR}; }
+
 // The plan's arrays with the partial-sum planes in blocks of columns, or in
 // grid order where the blocks' padding alone would push the need past the
 // allocation-free solve's fixed array (with or without the angular field).
 bte_status build_plan_impl(bte_ctx* h, const Plan& pl) {
-  // (the choice made while a plan was only counted holds when it is built:
-  // a bound workspace was sized for it)
-  const bool known = h->part_order == h->order && h->part_plan.G == pl.G && h->part_plan.R == pl.R &&
-                     h->part_plan.P == pl.P && h->part_plan.C == pl.C && h->part_plan.NR == pl.NR;
-  if (!known) h->part_blocks = true;
+  // (a plan's choice holds whenever the plan is built again, when it was only
+  // counted before or returned to after another was rejected: a workspace was
+  // sized for it)
+  const auto key = plan_key(h, pl);
+  const auto known = h->part_choice.find(key);
+  h->part_blocks = known == h->part_choice.end() || known->second;
   bte_status s = build_plan_arrays(h, pl);
-  if (s != BTE_OK || known) return s;
+  if (s != BTE_OK || known != h->part_choice.end()) return s;
   const long long lim = (long long)kStaticScratchBytes, need = (long long)(h->need_static + h->need_plan);
   const long long with = need + (long long)h->need_store;
   if ((need > lim && need - h->part_extra <= lim) ||
       (with > lim && with - h->part_extra - h->store_extra <= lim)) {
     h->part_blocks = false;
     s = build_plan_arrays(h, pl);
+    if (s != BTE_OK) return s;
   }
-  h->part_plan = h->plan;
-  h->part_order = s == BTE_OK ? h->order : 0;
+  h->part_choice.emplace(key, h->part_blocks);
+  h->part_choice.emplace(plan_key(h, h->plan), h->part_blocks);  // (as it was completed)
   return s;
 }
 
@@ -1122,6 +1129,32 @@ bte_status build_plan(bte_ctx* h, const Plan& pl) {
     return build_plan_impl(h, Plan(h->plan));
   }
   return build_plan_impl(h, pl);
+}
+
+bte_status build_static(bte_ctx* h);
+
+// Back to the plan (and face order) in force before one that was rejected.
+// Only memory of the handle's own that is gone meanwhile or a HIP error can
+// keep it from being built again: the handle then holds no device arrays, and
+// its next call makes them or returns the error; one bound to a workspace
+// refuses calls until a workspace is bound again. The message stays that of
+// the rejection.
+void restore_plan(bte_ctx* h, const Plan& old, int order) {
+  const std::string msg = g_err;
+  h->order = order;
+  if (build_plan(h, old) != BTE_OK) {
+    h->ws_lost = h->pool_mode == DevPool::ARENA;
+    h->ppool.reset();
+    h->spool.reset();
+    h->ws_base = nullptr;
+    h->ws_cap = 0;
+    h->ws_store = false;
+    h->pool_mode = DevPool::COUNT;
+    h->plan = old;
+    h->sched_valid = false;
+    if (build_static(h) == BTE_OK) (void)build_plan_impl(h, old);
+  }
+  g_err = msg;
 }
 
 // The default plan of the handle's order, or the base plan where only that one
@@ -1276,6 +1309,10 @@ bte_status build_static(bte_ctx* h) {
 // far, in memory of its own (no workspace bound).
 bte_status ensure_device(bte_ctx* h) {
   if (h->pool_mode != DevPool::COUNT) return BTE_OK;
+  if (h->ws_lost) {
+    set_err("the handle's arrays in its bound workspace were lost in a failed plan change: bind a workspace again");
+    return BTE_ERR_WORKSPACE;
+  }
   h->pool_mode = DevPool::OWNED;
   bte_status s = build_static(h);
   if (s == BTE_OK) s = build_plan_impl(h, h->plan);
@@ -1834,9 +1871,9 @@ bte_status apply_tune_cache(bte_ctx* h, const char* path, const double* d_Q, hip
     const Plan old = h->plan;
     bte_status s = build_plan(h, pl);
     if (s != BTE_OK) {
-      const std::string e = g_err;
-      (void)build_plan(h, old);
+      restore_plan(h, old, h->order);
       h->auto_plan = was_auto;
+      const std::string e = g_err;
       set_err("autotune cache %s: stored plan rejected: %s", path, e.c_str());
     }
     return s;
@@ -1871,6 +1908,7 @@ bte_status bind_impl(bte_ctx* h, void* d_ws, size_t bytes) {
   h->spool.reset();
   h->ws_base = static_cast<char*>(d_ws);
   h->ws_cap = d_ws ? bytes : 0;
+  h->ws_lost = false;
   h->ws_store = d_ws && bytes >= need + h->need_store;
   if (!d_ws) {
     // unbound: the handle's own memory is made by the next call that needs it
@@ -2169,12 +2207,7 @@ bte_status bte_set_order(bte_handle h, int order) {
   }
   h->order = order;
   bte_status s = build_plan(h, p);
-  if (s != BTE_OK) {
-    const std::string e = g_err;
-    h->order = old_order;
-    (void)build_plan(h, old);
-    g_err = e;
-  }
+  if (s != BTE_OK) restore_plan(h, old, old_order);
   return s;
 }
 
@@ -2192,13 +2225,8 @@ bte_status bte_set_plan(bte_handle h, const bte_plan* plan) {
   if (plan->NR) p.NR = plan->NR < 0 ? 0 : plan->NR;  // 3D: NR < 0 selects the pencil-block layout
   const Plan old = h->plan;
   bte_status s = build_plan(h, p);
-  if (s != BTE_OK) {
-    const std::string e = g_err;
-    (void)build_plan(h, old);
-    g_err = e;
-  } else {
-    h->auto_plan = false;
-  }
+  if (s != BTE_OK) restore_plan(h, old, h->order);
+  else h->auto_plan = false;
   return s;
 }
 
@@ -2598,7 +2626,10 @@ bte_status autotune_impl(bte_ctx* h, const double* d_Q, int n_iters, hipStream_t
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   bte_status s = build_plan(h, bestp);
-  if (s != BTE_OK) return s;
+  if (s != BTE_OK) {
+    restore_plan(h, keep, h->order);
+    return s;
+  }
   h->auto_plan = false;
   if (best) *best = bestp;
   return BTE_OK;

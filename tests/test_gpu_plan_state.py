@@ -1,0 +1,57 @@
+"""A handle's state around plan changes: the order of the cells in the
+partial-sum planes, a plan that is rejected, and what a bound workspace holds.
+Fields against the FP64 oracle to 1e-10 of the largest deviation (FP64 sums of
+a few thousand terms), or equal bit for bit where the same plan runs twice.
+"""
+import numpy as np
+import pytest
+
+import bte_inputs as bi
+import oracle
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+LIMIT = 64 << 20  # the allocation-free solve's array
+
+
+def narrow():
+    """Nine columns: in blocks of 8 columns the planes take 16/9 of the grid
+    order's bytes, and only grid order stays within the allocation-free array."""
+    return bi.random_box_2d(9, 250, seed=2, n_bands=15, n_theta=8, n_phi=8, hole=False, kinds=(0, 0))
+
+
+def blocked_plane_bytes(s, p, es):
+    """The planes' bytes in blocks of 8 columns (2D, an even number of ordinates per octant and band)."""
+    jobs = p.B * (p.M // 2) // s.plan()["P"]
+    cells = -(-p.n[0] // 8) * 8 * p.n[1]
+    return 3 * jobs * (-(-cells // 256) * 256) * es
+
+
+def test_rejected_plan_keeps_the_plane_order(hip_lib):
+    """Grid order is chosen for this problem; a rejected plan in between must
+    not turn it into blocks, neither in the reported bytes nor, in a workspace
+    of exactly those bytes, in the arrays."""
+    p = narrow()
+    s = hip_lib.Solver(p, precision="fp64", plan=dict(G=1, R=1, P=4, NR=2))
+    n0, before = s.workspace_bytes(False), s.plan()
+    assert n0 <= LIMIT < blocked_plane_bytes(s, p, 8)
+    for bad in (dict(P=3), dict(NR=3), dict(R=4, P=4)):
+        with pytest.raises(hip_lib.BTEError):
+            s.set_plan(**bad)
+        assert s.workspace_bytes(False) == n0 and s.plan() == before
+    Q = torch.tensor(p.Q, device="cuda")
+    T0 = torch.empty(p.ncell, dtype=torch.float64, device="cuda")
+    s.solve_noalloc(Q, T0, tol=0.0, max_iters=4, check_every=4)
+    r = oracle.solve(p, tol=0.0, max_iters=4)
+    act = p.mask > 0
+    assert np.abs(T0.cpu().numpy() - r["T"])[act].max() < 1e-10 * np.abs(r["T"] - p.T_ref)[act].max()
+    ws = torch.empty(n0, dtype=torch.uint8, device="cuda")
+    s.bind_workspace(ws)
+    for bad in (dict(P=3), dict(P=1)):  # no such plan; a plan that does not fit
+        with pytest.raises(hip_lib.BTEError):
+            s.set_plan(**bad)
+        assert s.plan() == before
+        T, _, _ = s.solve(Q, tol=0.0, max_iters=4, check_every=4)
+        assert torch.equal(T, T0)
+    s.close()
