@@ -660,18 +660,21 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
     I.part_jg = 0;
     if (h->dim == 3 && (size_t)I.part_ld * n_bund * es > (256ull << 20))
       while ((1 << I.part_jg) < n_bund && ((size_t)I.part_ld << (I.part_jg + 1)) * es < (1ull << 31)) ++I.part_jg;
-    HIPCHK(pp.alloc(&pt, (size_t)h->nacc_max * part_plane_len(n_bund, I.part_jg, I.part_ld) * es));
+    // (in blocks of columns the planes also hold the grid-order positions for a
+    // moment, one per octant and cell: more than the sums where few octants have
+    // ordinates, as with directions along the axes only)
+    const size_t part_bytes = std::max<size_t>((size_t)h->nacc_max * part_plane_len(n_bund, I.part_jg, I.part_ld) * es,
+                                               blocks ? S.pos.size() * 4 : 0);
+    HIPCHK(pp.alloc(&pt, part_bytes));
     I.d_part = pt;
     if (blocks && pp.mode != DevPool::COUNT) {
-      // the grid-order positions wait in the planes, which every octant has a
-      // job in; the null stream orders the kernel before the copies that follow
+      // the null stream orders the kernel before the copies that follow
       HIPCHK(hipMemcpy(I.d_part, S.pos.data(), S.pos.size() * 4, hipMemcpyHostToDevice));
       HIPCHK(launch_plane_tables(po, I.hi.ncell, S.n_oct, reinterpret_cast<const int*>(I.d_part), I.d_pos, I.d_cell_of,
                                  I.d_sched, (long long)S.sched.size(), nullptr));
     }
     const int ld0 = (I.hi.ncell + kPartBlk - 1) / kPartBlk * kPartBlk;
-    h->part_extra += al256((size_t)h->nacc_max * part_plane_len(n_bund, I.part_jg, I.part_ld) * es) -
-                     al256((size_t)h->nacc_max * part_plane_len(n_bund, I.part_jg, ld0) * es);
+    h->part_extra += al256(part_bytes) - al256((size_t)h->nacc_max * part_plane_len(n_bund, I.part_jg, ld0) * es);
     h->store_extra += al256((size_t)n_grp_inst * I.n_part * pl.G * es) -
                       al256((size_t)n_grp_inst * I.hi.ncell * pl.G * es);
     I.d_store = nullptr;

@@ -55,3 +55,24 @@ def test_rejected_plan_keeps_the_plane_order(hip_lib):
         T, _, _ = s.solve(Q, tol=0.0, max_iters=4, check_every=4)
         assert torch.equal(T, T0)
     s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("axes", [((0, 0, 1),), ((1, 0, 0), (0, 0, 1)), ((0, 1, 0),)], ids=["z", "xz", "y"])
+def test_few_octants_stay_in_the_workspace(hip_lib, precision, axes):
+    """Directions along the axes leave octants without ordinates, so that the
+    planes are smaller than the tables made in them: in a workspace of exactly
+    the reported bytes nothing behind it is written."""
+    p = bi.square_2d(70, L=0.2e-6, n_bands=1, n_theta=1, n_phi=1)
+    s = np.array([np.array(a, dtype=float) * g for a in axes for g in (1, -1)])
+    p = p.replace(s=s, w=np.full(len(s), 4 * np.pi / len(s)))
+    h = hip_lib.Solver(p, precision=precision)
+    n = h.workspace_bytes(False)
+    ws = torch.full((n + (1 << 20),), 0xA5, dtype=torch.uint8, device="cuda")
+    h.bind_workspace(ws[:n])
+    T, _, _ = h.solve(torch.tensor(p.Q, device="cuda"), tol=0.0, max_iters=4, check_every=4)
+    assert (ws[n:] == 0xA5).all()
+    h.close()
+    r = oracle.solve(p, tol=0.0, max_iters=4)
+    tol = 1e-10 if precision == "fp64" else 1e-4
+    assert np.abs(T.cpu().numpy() - r["T"]).max() < tol * np.abs(r["T"] - p.T_ref).max()
