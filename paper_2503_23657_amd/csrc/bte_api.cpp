@@ -374,6 +374,11 @@ std::vector<int2> period_bases(const Schedule& S, const PlaneOrder& po, int bs, 
   return pb;
 }
 
+// Planes a rows-per-lane sweep stages: with one ordinate per lane one plane,
+// double-buffered, whatever the sums it writes (they are multiples of it); else
+// every sum's, at least two (a single one is double-buffered).
+int staged_planes(int G, int nacc) { return G == 1 ? 2 : std::max(2, nacc); }
+
 // (Re)build everything that depends on the plan: schedules, group tables and
 // the plan-dependent arrays.
 bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
@@ -841,8 +846,7 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
   if (!L3 || R3) {
     // 1D/2D: ring [P][R][W_max + 1][G], cell ids [2][R][kC2][72], inflow
     // [P*R][2][E], outflow [P*R][o_max], staging [planes][P*R][kC2][64*NR + 8
-    // dwords] with max(2, nacc) planes (double-buffered for the
-    // temperature-only sweep)
+    // dwords] (staged_planes)
     int E = 64;
     for (auto& I : h->inst) E = std::max(E, I.sch.in_E);
     // (the 3D rows layout has no strip ring, forms its plane indices from the
@@ -857,8 +861,17 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
     off += R3 ? 0 : al((size_t)P * R * o_max * es);
     sa.lds_stage = (int)off;
     h->lds_stage_plane = al((size_t)P * R * kC2 * stage_row(pl.NR, (int)es) * es);
-    off += (size_t)std::max(2, h->nacc_max) * h->lds_stage_plane;
+    off += (size_t)staged_planes(G, h->nacc_max) * h->lds_stage_plane;
     sa.lds_total = (int)off;
+    if (R3 && es == 8 && pl.NR == 2 && P == 8) {
+      // never offered: the planes of every sum did not fit. With one plane
+      // staged small boundary tables leave it the LDS, and though its 256
+      // registers spill it is the faster at first order (100x100x30, 1920
+      // groups 3076 -> 2215 us an iteration, 20x70x20 441 -> 435; second order
+      // 1364 -> 1429); what was refused stays refused
+      set_err("eight waves with two FP64 rows per lane need %zu bytes of LDS and spill registers: P is at most 4", off);
+      return BTE_ERR_INVALID;
+    }
     if (off > 160 * 1024 - 64) {
       set_err("plan needs %zu bytes of LDS (limit 160 KiB): reduce P, R, NR or G", off);
       return BTE_ERR_INVALID;
@@ -1052,20 +1065,23 @@ Plan basic_plan(const bte_ctx* h) {
 //       diffuse walls, 160 groups: 196 -> 175, 179 -> 158; at 960 groups it is
 //       slower (FP64 326 -> 389, FP32 192 -> 204).
 //     FP64 else, more than two groups per CU: two rows per lane in one slot,
-//       four waves to a plane. 256^2, 960 groups 302 -> 190; at fewer it wins or
-//       loses with the size (256^2, 480 groups 161 -> 153, but the solve and
-//       adjoint of 183^2, 448 groups 23.0 -> 25.1 ms).
+//       four waves to a plane. 256^2, 960 groups 302 -> 190 (four rows and four
+//       waves: 182); at fewer it wins or loses with the size (256^2, 480 groups
+//       161 -> 153, but the solve and adjoint of 183^2, 448 groups 23.0 -> 25.1 ms).
 //   2D, first order, more than four groups per CU (batches): with several
 //     workgroups to a CU a step's time goes with its rows, so the rows per lane
 //     are those with the least steps times the measured cost of one (FP32 0.37 :
-//     0.53 : 1 for 1, 2 and 4 rows, FP64 0.28 : 0.52 : 1; four waves to a plane,
-//     which four rows in FP64 have no LDS for). Batches of squares of 33 to 159
-//     rows and columns: 64 in FP32 1406 -> 981, 8 in FP32 183 -> 131, 24 in FP64
-//     1082 -> 619.
+//     0.53 : 1 for 1, 2 and 4 rows, FP64 0.28 : 0.52 : 1; four waves to a plane).
+//     FP64 takes one or two: four rows have LDS for one such workgroup on a CU
+//     only (256^2, 3840 groups 743 with two rows, 711 with four; 200x300, 1920
+//     groups 378 with one, 481 with two, 493 with four). Batches of squares of
+//     33 to 159 rows and columns: 64 in FP32 1406 -> 981, 8 in FP32 183 -> 131,
+//     24 in FP64 1082 -> 619.
 //   3D: FP32 with no more groups than CUs: 4 waves share a plane instead of 8.
 //     37x29x23, 160 groups 181 -> 176, 60x60x50, 256 groups 639 -> 628; 46x45x35,
 //     512 groups 552 -> 561. FP64 with more than four groups per CU: 8 instead
 //     of 4. 46x45x35, 1920 groups 1197 -> 1018; 23x23x18, 960 groups 211 -> 225.
+//     (Two rows per lane in FP64 are not offered with 8 and stay with 4.)
 Plan default_plan(const bte_ctx* h, int order) {
   Plan pl = basic_plan(h);
   const long long n = (long long)h->B * (long long)h->ords.size() * (long long)h->inst.size(), cu = h->n_cu;
@@ -1435,9 +1451,7 @@ bte_status enqueue_sweep(bte_ctx* h, bool adj, int nacc, int mode, int force, hi
   a.grp_t = adj ? h->d_gt_a : h->d_gt_f;
   a.force = force;
   if (h->dim < 3 || h->l3r) {
-    // one ordinate per lane stages one plane, double-buffered, whatever nacc
-    const int planes = h->plan.G == 1 ? 2 : std::max(2, nacc);
-    const size_t lds = (size_t)a.lds_stage + (size_t)planes * h->lds_stage_plane;
+    const size_t lds = (size_t)a.lds_stage + (size_t)staged_planes(h->plan.G, nacc) * h->lds_stage_plane;
     if (h->l3r)
       HIPCHK(launch_sweep3r(h->precision, h->plan.NR, h->plan.P, nacc, mode, a, h->grid, h->block, lds, st));
     else

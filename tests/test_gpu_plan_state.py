@@ -76,3 +76,48 @@ def test_few_octants_stay_in_the_workspace(hip_lib, precision, axes):
     r = oracle.solve(p, tol=0.0, max_iters=4)
     tol = 1e-10 if precision == "fp64" else 1e-4
     assert np.abs(T.cpu().numpy() - r["T"]).max() < tol * np.abs(r["T"] - p.T_ref).max()
+
+
+def porous(nx, ny, nz, **kw):
+    """One cell in ten missing at random: up to 256 inflow entries a chunk."""
+    p = bi.random_box_3d(nx, ny, nz, seed=1, hole=False, kinds=(0, 1), **(kw or dict(n_bands=2, n_theta=2, n_phi=2)))
+    mask = (np.random.default_rng(5).random(p.ncell) < 0.9).astype(np.uint8)
+    fbc = bi.face_bc_from_mask(p.n, 3, mask, lambda i, j, k, f: 0 if f == 4 else 1)
+    return p.replace(mask=mask, face_bc=fbc, Q=p.Q * mask)
+
+
+@pytest.mark.parametrize("make,plan", [
+    (lambda: bi.random_box_2d(16, 131, seed=2, n_bands=3, n_theta=2, n_phi=2, kinds=(0, 1)), dict(P=4, NR=4)),
+    (lambda: bi.random_box_2d(23, 259, seed=3, n_bands=2, n_theta=2, n_phi=1, kinds=(0, 2)), dict(P=4, NR=4)),
+    (lambda: bi.random_box_2d(2001, 70, seed=2, n_bands=2, n_theta=2, n_phi=1, hole=False, kinds=(0, 1)),
+     dict(P=4, NR=2)),
+    (lambda: porous(24, 64, 8), dict(P=8, NR=1)),
+], ids=["rows4", "strips", "wide", "porous"])
+def test_plans_within_the_lds_run(hip_lib, make, plan):
+    """FP64 plans that one staged plane (double-buffered) leaves room for and
+    three or four would not: fields of both face orders against the oracle,
+    gradients against two waves per workgroup (both sum the same FP64 terms in
+    another order, iterated to 1e-12)."""
+    p = make()
+    Q = torch.tensor(p.Q, device="cuda")
+    act = p.mask > 0
+    s = hip_lib.Solver(p, precision="fp64", plan=dict(G=1, R=1, **plan))
+    assert {k: s.plan()[k] for k in plan} == plan
+    for order in (1, 2):
+        s.set_order(order)
+        T, q, _ = s.solve(Q, tol=0.0, max_iters=4, check_every=4)
+        r = oracle.solve(p, tol=0.0, max_iters=4, order=order)
+        rq = r["q"].reshape(p.ncell, p.dim)
+        assert np.abs(T.cpu().numpy() - r["T"])[act].max() < 1e-10 * np.abs(r["T"] - p.T_ref)[act].max()
+        assert np.abs(q.cpu().numpy() - rq)[act].max() < 1e-10 * np.abs(rq).max()
+    s.close()
+    g = torch.tensor(np.cos(np.arange(p.ncell)) * p.mask, device="cuda")
+    out = []
+    for pl in (plan, dict(P=2, NR=1)):
+        s = hip_lib.Solver(p, precision="fp64", plan=dict(G=1, R=1, **pl))
+        s.solve(Q, tol=1e-12, store_state=True)
+        dtau, dQ, _ = s.adjoint(g, tol=1e-12)
+        s.close()
+        out.append((dtau, dQ.cpu().numpy()))
+    for a, b in zip(*out):
+        assert np.abs(a - b).max() < 1e-9 * np.abs(b).max()
