@@ -784,6 +784,10 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
       ja.push_back(JobDev{(int)k, I.grp0 + gs.bundle_first[b], b, o ^ (n_oct - 1)});
     }
   }
+  // (schedules and groups hold whatever becomes of the rest: a plan refused for
+  // its LDS leaves them to the one that follows)
+  h->sched_plan = pl;
+  h->sched_valid = true;
   // larger instances first (the queue hands out jobs in order)
   auto work = [&](const JobDev& j) { return (long long)h->inst[j.inst].sch.T * h->inst[j.inst].sch.R; };
   std::stable_sort(jf.begin(), jf.end(), [&](const JobDev& a, const JobDev& b) { return work(a) > work(b); });
@@ -974,8 +978,6 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
 // plan and its workspace bytes.
 bte_status finish_plan(bte_ctx* h, const Plan& pl, DevPool& pp) {
   h->plan = pl;
-  h->sched_plan = pl;
-  h->sched_valid = true;
   h->need_plan = pp.used;
   // the angular field kept for the adjoint: part of a bound workspace when it
   // was sized for it, else allocated by the first solve that stores it

@@ -121,3 +121,23 @@ def test_plans_within_the_lds_run(hip_lib, make, plan):
         out.append((dtau, dQ.cpu().numpy()))
     for a, b in zip(*out):
         assert np.abs(a - b).max() < 1e-9 * np.abs(b).max()
+
+
+def test_refused_default_keeps_its_schedules(hip_lib):
+    """FP64 with two rows per lane and many groups: the default plan's eight
+    waves are refused after its schedules are made, and the plan that follows
+    takes them over. Creating the handle then takes about as long as in FP32,
+    whose first plan holds (twice as long if the schedules were made again)."""
+    import time
+    p = bi.random_box_3d(40, 100, 40, seed=1, n_bands=9, n_theta=4, n_phi=4)
+    best = {}
+    for _ in range(3):
+        for precision in ("fp32", "fp64"):
+            t = time.perf_counter()
+            s = hip_lib.Solver(p, precision=precision)
+            t = time.perf_counter() - t
+            best[precision] = min(t, best.get(precision, t))
+            plan = s.plan()
+            s.close()
+    assert (plan["P"], plan["NR"]) == (4, 2)
+    assert best["fp64"] < 1.6 * best["fp32"], best
