@@ -130,8 +130,11 @@ typedef struct {
       are assigned for the fewest boundary entries; taken when the problem
       fits, with the NR the grid needs), reported back as the rows per lane
       used.
-   Zero fields mean "keep the current value". A shape whose LDS need exceeds
-   the per-workgroup limit is rejected with BTE_ERR_INVALID. */
+   Zero fields mean "keep the current value"; on a handle that was given no plan
+   that of one strip of 64*NR rows with P = 4 waves in FP32 and 2 in FP64 (3D:
+   8 and 4), whatever plan the handle chose for itself. A shape whose LDS need
+   exceeds the per-workgroup limit is rejected with BTE_ERR_INVALID, and so are
+   eight waves with two FP64 rows per lane in 3D. */
 typedef struct { int G, R, P, C, NR; } bte_plan;
 
 /* Options of a solve or adjoint (Methods, "Iterative matrix formulation and
@@ -204,7 +207,9 @@ bte_status bte_create(const bte_geometry* geom, const bte_bands* bands,
 
 /* Device bytes the handle needs for its current plan: *bytes. with_adjoint = 1
    adds the angular field that a solve with store_angular keeps for
-   bte_adjoint. A later bte_set_plan or bte_autotune may change the figure. */
+   bte_adjoint. A handle that was given no plan reports enough for the plan
+   that bte_set_plan completes a partial one from, too. A later bte_set_plan or
+   bte_autotune may change the figure. */
 bte_status bte_workspace_bytes(bte_handle h, int with_adjoint, size_t* bytes);
 
 /* Bind caller-owned device memory (e.g. torch.empty(bytes, dtype=torch.uint8)

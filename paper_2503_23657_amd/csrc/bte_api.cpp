@@ -209,6 +209,7 @@ struct bte_ctx {
   bool ws_store = false;               // the bound workspace holds the adjoint's angular field
   bool ws_lost = false;                // a workspace was bound, but its arrays could not be rebuilt
   size_t need_static = 0, need_plan = 0, need_store = 0;  // workspace bytes of the current plan
+  size_t base_need[2] = {0, 0}, base_store[2] = {0, 0};   // those of the base plan, by face order (0: not counted)
   bool part_blocks = true;             // the build at hand orders the cells of its partial-sum planes in
                                        // blocks of columns (see plane_order), else in grid order
   std::map<std::array<int, 6>, bool> part_choice;  // that choice of every plan built so far (see plan_key)
@@ -1326,6 +1327,44 @@ bte_status build_static(bte_ctx* h) {
   return BTE_OK;
 }
 
+// Workspace bytes of a handle: those of its plan, and while that is the default
+// one at least those of the base plan too. A plan given in part is completed
+// from the base plan, and plan caches hold it; neither may stop to fit because
+// the default plan needs less (FP64 sections up to 128 rows: half the planes).
+// The base plan is counted on a handle of its own: the arrays of this one stay.
+bte_status workspace_need(bte_ctx* h, bool with_adjoint, size_t* bytes) {
+  size_t need = h->need_static + h->need_plan, store = h->need_store;
+  const Plan &a = h->plan, &b = h->base_plan;
+  if (h->auto_plan && !(a.G == b.G && a.R == b.R && a.P == b.P && a.C == b.C && a.NR == b.NR)) {
+    size_t &bn = h->base_need[h->order - 1], &bs = h->base_store[h->order - 1];
+    if (bn == 0) {
+      bte_ctx c;
+      c.precision = h->precision;
+      c.dim = h->dim;
+      c.B = h->B;
+      c.v = h->v;
+      c.tau = h->tau;
+      c.C = h->C;
+      c.ords = h->ords;
+      c.t0 = h->t0;
+      c.n_cu = h->n_cu;
+      c.order = h->order;
+      c.inst.resize(h->inst.size());
+      for (size_t k = 0; k < c.inst.size(); ++k) c.inst[k].hi = h->inst[k].hi;
+      const std::string msg = g_err;
+      const bool ok = build_static(&c) == BTE_OK && build_plan_impl(&c, b) == BTE_OK;
+      g_err = msg;
+      bn = ok ? c.need_static + c.need_plan : need;  // (pencil blocks have no second order)
+      bs = ok ? c.need_store : store;
+    }
+    store = std::max(need + store, bn + bs);
+    need = std::max(need, bn);
+    store -= need;
+  }
+  *bytes = need + (with_adjoint ? store : 0);
+  return BTE_OK;
+}
+
 // Build the device state of a handle whose arrays have only been counted so
 // far, in memory of its own (no workspace bound).
 bte_status ensure_device(bte_ctx* h) {
@@ -1910,13 +1949,13 @@ bte_status apply_tune_cache(bte_ctx* h, const char* path, const double* d_Q, hip
   return BTE_OK;
 }
 
-// Carve every device array of h from [d_ws, d_ws + bytes), or unbind (d_ws NULL).
-bte_status bind_impl(bte_ctx* h, void* d_ws, size_t bytes) {
+// Carve every device array of h from [d_ws, d_ws + bytes), or unbind (d_ws
+// NULL); need, with: the bytes it takes without and with the angular field.
+bte_status bind_impl(bte_ctx* h, void* d_ws, size_t bytes, size_t need, size_t with) {
   if (d_ws && reinterpret_cast<uintptr_t>(d_ws) % kWsAlign) {
     set_err("workspace must be %zu-byte aligned", kWsAlign);
     return BTE_ERR_INVALID;
   }
-  const size_t need = h->need_static + h->need_plan;
   if (d_ws && bytes < need) {
     set_err("workspace of %zu bytes is smaller than the %zu the handle needs", bytes, need);
     return BTE_ERR_WORKSPACE;
@@ -1928,7 +1967,7 @@ bte_status bind_impl(bte_ctx* h, void* d_ws, size_t bytes) {
   h->ws_base = static_cast<char*>(d_ws);
   h->ws_cap = d_ws ? bytes : 0;
   h->ws_lost = false;
-  h->ws_store = d_ws && bytes >= need + h->need_store;
+  h->ws_store = d_ws && bytes >= with;
   if (!d_ws) {
     // unbound: the handle's own memory is made by the next call that needs it
     h->pool_mode = DevPool::COUNT;
@@ -2046,7 +2085,7 @@ bte_status bind_static_scratch(bte_ctx* h) {
     }
   }
   g_scratch_owner[dev] = nullptr;
-  bte_status s = bind_impl(h, ws, kStaticScratchBytes);
+  bte_status s = bind_impl(h, ws, kStaticScratchBytes, need, need + h->need_store);
   if (s == BTE_OK) g_scratch_owner[dev] = h;
   return s;
 }
@@ -2178,8 +2217,7 @@ bte_status bte_workspace_bytes(bte_handle h, int with_adjoint, size_t* bytes) {
     set_err("null handle or output");
     return BTE_ERR_INVALID;
   }
-  *bytes = h->need_static + h->need_plan + (with_adjoint ? h->need_store : 0);
-  return BTE_OK;
+  return workspace_need(h, with_adjoint != 0, bytes);
 }
 
 bte_status bte_bind_workspace(bte_handle h, void* d_ws, size_t bytes) {
@@ -2188,8 +2226,12 @@ bte_status bte_bind_workspace(bte_handle h, void* d_ws, size_t bytes) {
     set_err("null handle");
     return BTE_ERR_INVALID;
   }
+  size_t need = 0, with = 0;
+  bte_status s = d_ws ? workspace_need(h, false, &need) : BTE_OK;
+  if (s == BTE_OK && d_ws) s = workspace_need(h, true, &with);
+  if (s != BTE_OK) return s;
   release_static_scratch(h);
-  return bind_impl(h, d_ws, bytes);
+  return bind_impl(h, d_ws, bytes, need, with);
 }
 
 bte_status bte_set_tau(bte_handle h, const double* h_tau) {

@@ -141,3 +141,51 @@ def test_refused_default_keeps_its_schedules(hip_lib):
             s.close()
     assert (plan["P"], plan["NR"]) == (4, 2)
     assert best["fp64"] < 1.6 * best["fp32"], best
+
+
+def section():
+    return bi.random_box_2d(61, 100, seed=2, n_bands=15, n_theta=4, n_phi=2, kinds=(0, 1))
+
+
+def tuned(hip_lib, p, path, plan):
+    """A plan cache whose line for p holds `plan`."""
+    s = hip_lib.Solver(p, precision="fp64")
+    s.solve(torch.tensor(p.Q, device="cuda"), tol=0.0, max_iters=1, autotune_cache=path)
+    s.close()
+    key = open(path).read().split(" plan ")[0]
+    open(path, "w").write(key + " plan " + " ".join(str(plan[k]) for k in ("G", "R", "P", "C", "NR")) + "\n")
+
+
+@pytest.mark.parametrize("adjoint", [False, True])
+@pytest.mark.parametrize("how", ["G", "P", "cache"])
+def test_workspace_holds_the_plan_partial_ones_start_from(hip_lib, tmp_path, how, adjoint):
+    """The default plan of an FP64 section shares its planes among four waves,
+    a plan given in part among two: a workspace of exactly the reported bytes
+    takes both, and a plan cache that holds the latter."""
+    p = section()
+    Q = torch.tensor(p.Q, device="cuda")
+    base = dict(G=1, R=1, P=2, C=8, NR=2)
+    opt = dict(tol=0.0, max_iters=4, check_every=4, store_state=adjoint)
+    s = hip_lib.Solver(p, precision="fp64")
+    assert s.plan() == dict(base, P=4)
+    s.bind_workspace(torch.empty(s.workspace_bytes(adjoint), dtype=torch.uint8, device="cuda"))
+    s.solve(Q, **opt)
+    if how == "cache":
+        opt["autotune_cache"] = str(tmp_path / "plans")
+        tuned(hip_lib, p, opt["autotune_cache"], base)
+    else:
+        s.set_plan(**{how: base[how]})
+        assert s.plan() == base
+    T, q, _ = s.solve(Q, **opt)
+    assert s.plan() == base
+    n = s.workspace_bytes(adjoint)
+    s.close()
+    r = oracle.solve(p, tol=0.0, max_iters=4)
+    act = p.mask > 0
+    assert np.abs(T.cpu().numpy() - r["T"])[act].max() < 1e-10 * np.abs(r["T"] - p.T_ref)[act].max()
+    # a plan that was given reports its own bytes
+    s = hip_lib.Solver(p, precision="fp64", plan=dict(P=2))
+    assert s.workspace_bytes(adjoint) == n
+    s.set_plan(P=4)
+    assert s.workspace_bytes(adjoint) < n
+    s.close()
