@@ -252,6 +252,16 @@ bte_status bte_set_order(bte_handle h, int order);
 bte_status bte_set_plan(bte_handle h, const bte_plan* plan);
 bte_status bte_get_plan(bte_handle h, bte_plan* plan);
 
+/* Which of the alternatives that follow from the problem and the plan the
+   handle runs (host only; for tests and reports): *paths gets BTE_PATH_* bits. */
+enum {
+  BTE_PATH_PLANE_BLOCKS = 1, /* partial-sum planes in blocks of 8 columns (else grid order) */
+  BTE_PATH_FILM = 2,         /* 1D: one launch runs all iterations of a chunk, each sweep a scan */
+  BTE_PATH_CORR_MARCH = 4    /* order 2: the correction marches over the stored field (else it
+                                gathers through a stencil table) */
+};
+bte_status bte_get_paths(bte_handle h, unsigned* paths);
+
 /* Time candidate kernel shapes on this problem and keep the fastest; writes it
    to *best (may be NULL). Each candidate runs n_iters whole source iterations
    (sweep, finalize, diffuse-wall update) after one warm-up iteration, from a

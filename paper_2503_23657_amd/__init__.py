@@ -103,6 +103,7 @@ bte_set_tau = _sig("bte_set_tau", _S, [_H, _P])
 bte_set_order = _sig("bte_set_order", _S, [_H, ctypes.c_int])
 bte_set_plan = _sig("bte_set_plan", _S, [_H, ctypes.POINTER(Plan)])
 bte_get_plan = _sig("bte_get_plan", _S, [_H, ctypes.POINTER(Plan)])
+bte_get_paths = _sig("bte_get_paths", _S, [_H, ctypes.POINTER(ctypes.c_uint)])
 bte_autotune = _sig("bte_autotune", _S, [_H, _P, ctypes.c_int, _P, ctypes.POINTER(Plan)])
 bte_solve = _sig("bte_solve", _S, [_H, _P, _P, _P, _P, _P, ctypes.POINTER(Opts), _P, ctypes.POINTER(Report)])
 bte_solve_noalloc = _sig("bte_solve_noalloc", _S, [_H, _P, _P, _P, _P, _P, ctypes.POINTER(Opts), _P,
@@ -117,7 +118,7 @@ bte_destroy = _sig("bte_destroy", _S, [_H])
 
 EXPORTED = ["bte_version", "bte_last_error", "bte_validate", "bte_quadrature_gl_mu",
             "bte_quadrature_octant_gl", "bte_create", "bte_workspace_bytes", "bte_bind_workspace",
-            "bte_set_tau", "bte_set_order", "bte_set_plan", "bte_get_plan",
+            "bte_set_tau", "bte_set_order", "bte_set_plan", "bte_get_plan", "bte_get_paths",
             "bte_autotune", "bte_solve", "bte_solve_noalloc", "bte_adjoint", "bte_adjoint_dscale", "bte_time_sweep", "bte_batch_create",
             "bte_batch_solve", "bte_batch_adjoint", "bte_destroy"]
 
@@ -243,6 +244,12 @@ class _Workspace:
         self._ws = ws
 
 
+def _paths(h) -> set:
+    n = ctypes.c_uint()
+    _check(bte_get_paths(h, ctypes.byref(n)))
+    return {name for bit, name in ((1, "plane_blocks"), (2, "film"), (4, "corr_march")) if n.value & bit}
+
+
 class Solver(_Workspace):
     """One problem on the current HIP device (see bte_create).
 
@@ -289,6 +296,10 @@ class Solver(_Workspace):
         pl = Plan()
         _check(bte_get_plan(self._h, ctypes.byref(pl)))
         return pl.as_dict()
+
+    def paths(self) -> set:
+        """What the handle runs of "plane_blocks", "film" and "corr_march" (bte_get_paths)."""
+        return _paths(self._h)
 
     def set_tau(self, tau):
         t = _c(tau, np.float64)
@@ -410,6 +421,10 @@ class BatchSolver(_Workspace):
         pl = Plan()
         _check(bte_get_plan(self._h, ctypes.byref(pl)))
         return pl.as_dict()
+
+    def paths(self) -> set:
+        """As Solver.paths, of what every instance runs."""
+        return _paths(self._h)
 
     def autotune(self, n_iters=5, stream=None) -> dict:
         """bte_autotune on the whole batch (zero source in the timing runs)."""

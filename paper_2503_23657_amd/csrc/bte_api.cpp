@@ -2557,6 +2557,19 @@ bte_status bte_adjoint_dscale(bte_handle h, double* h_dJds) {
   return BTE_OK;
 }
 
+bte_status bte_get_paths(bte_handle h, unsigned* paths) {
+  if (!h || !paths) {
+    set_err("null handle or output");
+    return BTE_ERR_INVALID;
+  }
+  unsigned p = h->d_film ? BTE_PATH_FILM : 0u;
+  const auto all = [&](auto f) { return std::all_of(h->inst.begin(), h->inst.end(), f); };
+  if (all([](const Inst& I) { return I.d_cell_of != nullptr; })) p |= BTE_PATH_PLANE_BLOCKS;
+  if (h->order == 2 && all([](const Inst& I) { return I.ctab_ok; })) p |= BTE_PATH_CORR_MARCH;
+  *paths = p;
+  return BTE_OK;
+}
+
 bte_status bte_time_sweep(bte_handle h, int n_launches, void* hip_stream, double* h_ms, double* h_updates) {
   ErrClear clear_on_exit;
   if (!h || n_launches < 1 || !h_ms) {
