@@ -334,7 +334,10 @@ bte_status bte_adjoint_dscale(bte_handle h, double* h_dJds);
 /* Average device time (ms) of one launch of the forward sweep kernel on the
    current state, measured with HIP events around n_launches back-to-back
    launches on hip_stream; also returns the number of cell x ordinate x band
-   updates one launch performs. Requires a previous bte_solve. */
+   updates one launch performs. 1D films whose iterations one launch runs
+   (BTE_PATH_FILM): the time of one iteration (sweep, new temperature and lagged
+   walls) of a launch of n_launches; no state changes. Requires a previous
+   bte_solve. */
 bte_status bte_time_sweep(bte_handle h, int n_launches, void* hip_stream, double* h_ms,
                           double* h_updates);
 

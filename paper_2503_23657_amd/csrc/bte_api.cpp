@@ -1599,7 +1599,7 @@ bte_status enqueue_corr(bte_ctx* h, hipStream_t st) {
 }
 
 // n iterations of 1D films, as enqueue_chunk, in one launch.
-bte_status enqueue_film(bte_ctx* h, bool adj, int n, const bte_opts& o, hipStream_t st) {
+bte_status enqueue_film(bte_ctx* h, bool adj, int n, const bte_opts& o, hipStream_t st, int flags = 0) {
   FilmArgs a;
   a.inst = adj ? h->d_inst_a : h->d_inst_f;
   a.fin = adj ? h->d_fin_a : h->d_fin_f;
@@ -1609,7 +1609,7 @@ bte_status enqueue_film(bte_ctx* h, bool adj, int n, const bte_opts& o, hipStrea
   a.n_grp = (int)h->gs.band.size();
   a.g_split = (int)(std::find(h->gs.oct.begin(), h->gs.oct.end(), 1) - h->gs.oct.begin());
   a.n_iter = n;
-  a.flags = adj ? FIN_ADJ : 0;
+  a.flags = flags | (adj ? FIN_ADJ : 0);
   a.tol_T = o.tol_T;
   a.tol_q = adj ? 1.0 : o.tol_q;
   a.B = h->B;
@@ -2585,10 +2585,18 @@ bte_status bte_time_sweep(bte_handle h, int n_launches, void* hip_stream, double
   HIPCHK(hipEventCreate(&e0));
   HIPCHK(hipEventCreate(&e1));
   const int mode = h->order == 2 ? SWEEP_SECOND : SWEEP_PLAIN;
-  bte_status s = enqueue_sweep(h, false, 1, mode, 1, st);  // warm-up
+  // films that one launch iterates: n_launches iterations of it
+  const bte_opts film_opts{};
+  auto run = [&](int n) {
+    if (h->d_film) return enqueue_film(h, false, n, film_opts, st, FILM_TIMING);
+    bte_status r = BTE_OK;
+    for (int i = 0; i < n && r == BTE_OK; ++i) r = enqueue_sweep(h, false, 1, mode, 1, st);
+    return r;
+  };
+  bte_status s = run(1);  // warm-up
   if (s != BTE_OK) return s;
   HIPCHK(hipEventRecord(e0, st));
-  for (int i = 0; i < n_launches && s == BTE_OK; ++i) s = enqueue_sweep(h, false, 1, mode, 1, st);
+  s = run(n_launches);
   HIPCHK(hipEventRecord(e1, st));
   HIPCHK(hipEventSynchronize(e1));
   float ms = 0.f;

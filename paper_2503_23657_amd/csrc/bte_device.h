@@ -398,13 +398,14 @@ struct FilmArgs {
   int n_grp;                 // groups of an instance
   int g_split;               // first group of octant 1
   int n_iter;
-  int flags;                 // FIN_ADJ
+  int flags;                 // FIN_ADJ, FILM_TIMING
   double tol_T, tol_q;
   int B, rows;               // bands; inflow-table rows per band
   const int2* src;           // specular walls, as in SpecArgs
   const double* inv_wq;
   const int2* grp_ob;        // [2][B]
 };
+enum { FILM_TIMING = 256 };  // run even where the instance is done, and change no state
 constexpr int kFilmConst = 8;           // values per group kept in LDS
 constexpr int kFilmLds = 150 * 1024;    // most LDS a launch may ask for (160 KiB per CU)
 constexpr int kFilmCells = 1024;        // longest film: 16 cells per lane

@@ -66,7 +66,8 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
   const FinInst& F = A.fin[inst];
   const FilmInst& W = A.walls[inst];
   StatusDev* st = reinterpret_cast<StatusDev*>(I.status);
-  if (st->done) return;
+  const bool keep = !(A.flags & FILM_TIMING);
+  if (st->done && keep) return;
   const bool adj = (A.flags & FIN_ADJ) != 0;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = I.ncell, iter = st->iter, cur = iter & 1, nxt = (iter + A.n_iter) & 1;
@@ -194,7 +195,7 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
           u = s * W.inv_half[face];
         }
         sC[(size_t)g * kFilmConst + FC_IN] = sC[(size_t)g * kFilmConst + FC_DEN] * u;
-        if (last) ubf[(size_t)gi.w * I.n_bface + W.slot[face]] = (T)u;
+        if (last && keep) ubf[(size_t)gi.w * I.n_bface + W.slot[face]] = (T)u;
       }
     }
     __syncthreads();
@@ -208,7 +209,7 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
         if (c >= n) continue;
         const double v = total(c), m = sqrt(v * v), d = m - qm[p];
         qm[p] = m;
-        if (last) {
+        if (last && keep) {
           F.q[c] = v;
           F.qmag_prev[c] = m;
           res[2] += d * d;
@@ -218,6 +219,7 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
       __syncthreads();
     }
   }
+  if (!keep) return;
   // ---- the new state, in grid order and in both octants' layouts
   T* xq = reinterpret_cast<T*>(I.xq[nxt]);
   for (int c = tid; c < n; c += NT) {

@@ -126,3 +126,35 @@ def test_correction_path(hip_lib, make, plan, want):
     s.set_order(2)
     assert ("corr_march" in s.paths()) == want
     s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("kinds", [(0, 0), (0, 1), (0, 2)])
+def test_time_sweep_of_a_film(hip_lib, precision, kinds):
+    """The time reported is that of the kernel the solve runs (the general sweep
+    takes five times as long), and timing changes nothing: neither the state a
+    gradient starts from nor the output of an earlier solve."""
+    p = film(200, n_mu=32).replace(bc_kind=np.array(kinds, dtype=np.int32))
+    Q = torch.tensor(p.Q, device="cuda")
+    g = torch.tensor(np.cos(np.arange(p.ncell)), device="cuda")
+    out = []
+    for timed in (False, True):
+        s = hip_lib.Solver(p, precision=precision)
+        T, q, rep = s.solve(Q, tol=0.0, max_iters=800, store_state=True)
+        Tc, qc = T.clone(), q.clone()
+        if timed:
+            T.zero_(), q.zero_()
+            ms, updates = s.time_sweep(200)
+            assert updates == p.ncell * p.M * p.B
+            assert 800 * ms * 1e-3 < 1.5 * rep["seconds"], (ms, rep)
+            assert not T.any() and not q.any()
+            T2, q2, _ = s.solve(Q, T_init=Tc, tol=0.0, max_iters=8, store_state=True)
+        else:
+            T2, q2, _ = s.solve(Q, T_init=Tc, tol=0.0, max_iters=8, store_state=True)
+        if timed:
+            s.time_sweep(7)
+        dtau, dQ, _ = s.adjoint(g, tol=0.0, max_iters=16)
+        assert ("film_chunk" in s.sweep_kernel_name())
+        s.close()
+        out.append([x.cpu().numpy() for x in (Tc, qc, T2, q2, dQ)] + [dtau])
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
