@@ -538,6 +538,7 @@ __global__ void __launch_bounds__(L3 && !(NR == 2 && P <= 4 && sizeof(T) == 8) ?
     //      or dJ/dQ weight over its temperature weight), so one plane is
     //      staged and the write-out forms every plane's sum from it.
     constexpr bool PIPE = SP == 1;
+    static_assert(!L3 || PIPE, "the 3D sweep reads its outflows from the one staged plane");
     constexpr int PAIRS = kC2 / P;
     constexpr int NB = PIPE ? (PAIRS < kC2 / 2 ? PAIRS : kC2 / 2) : 1;
     // pairs per batch: the pipelined write-out splits the pairs over NB
@@ -727,7 +728,7 @@ __global__ void __launch_bounds__(L3 && !(NR == 2 && P <= 4 && sizeof(T) == 8) ?
     }
     T ev[kOPL];
     auto emit_read = [&](int c) BTE_INL {
-      const T* sb = stage + (size_t)(PIPE ? (c & 1) : 0) * plane_sz + (size_t)(p * R + r) * kC2 * RS;
+      const T* sb = stage + (size_t)(c & 1) * plane_sz + (size_t)(p * R + r) * kC2 * RS;
       const int rows = out_rows(och, och1);
       auto row = [&](auto m) BTE_INL {
         if (m == 0 || m < rows) ev[m] = sb[(unsigned)oe[m] >> 3];
@@ -1127,12 +1128,9 @@ __global__ void __launch_bounds__(L3 && !(NR == 2 && P <= 4 && sizeof(T) == 8) ?
         out_tot += out_cnt;
       }
       if constexpr (!PIPE) {
-        // single-buffered staging: write the chunk (and its outflows) out
-        // now, then wait for every reader before the next chunk stages again
-        if constexpr (L3) {
-          emit_read(ch);
-          emit_store(ch);
-        }
+        // single-buffered staging (two ordinates per lane, several sums): write
+        // the chunk out now, then wait for every reader before the next chunk
+        // stages again
 #pragma unroll
         for (int b = 0; b < PAIRS / MB; ++b) {
           wo_read(b, ch);
