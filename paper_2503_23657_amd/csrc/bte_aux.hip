@@ -677,8 +677,9 @@ hipError_t launch_spec_update(int prec, const SpecArgs& a, hipStream_t st) {
   if (n == 0) return hipSuccess;
   // one band per thread below two workgroups per CU; a thread for every band
   // everywhere reads the face tables once per band (specular walls of the
-  // half-size FinFET-like domain: 17.4 -> 18.4 ms per 24 iterations)
-  const dim3 grid(nblk(n), nblk(n) < 512 ? a.B : 1);
+  // half-size FinFET-like domain: 17.4 -> 18.4 ms per 24 iterations). The
+  // second dimension of a grid takes 65536 workgroups
+  const dim3 grid(nblk(n), nblk(n) < 512 && a.B <= 65536 ? a.B : 1);
   if (prec == BTE_PREC_FP32)
     hipLaunchKernelGGL(spec_update_kernel<float>, grid, dim3(256), 0, st, a);
   else

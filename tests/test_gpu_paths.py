@@ -158,3 +158,13 @@ def test_time_sweep_of_a_film(hip_lib, precision, kinds):
         s.close()
         out.append([x.cpu().numpy() for x in (Tc, qc, T2, q2, dQ)] + [dtau])
     assert all(np.array_equal(a, b) for a, b in zip(*out))
+
+
+def test_specular_update_of_many_bands(hip_lib):
+    """More bands than the second dimension of a grid takes workgroups."""
+    p = film(4, n_mu=2, bands=66001).replace(bc_kind=np.array([0, 2], dtype=np.int32))
+    s = hip_lib.Solver(p, precision="fp64")
+    assert "film" not in s.paths()
+    T, q, _ = s.solve(torch.tensor(p.Q, device="cuda"), tol=0.0, max_iters=4, check_every=4)
+    s.close()
+    check(p, T, q, "fp64", 4)
