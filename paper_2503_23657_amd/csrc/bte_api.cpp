@@ -817,9 +817,16 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
     h->d_gt_a = pb;
   }
   // 1D films in one launch per chunk (bte_film.hip): unmasked, first-order
-  // faces, one ordinate per group, within the kernel's registers and LDS. One
-  // workgroup then sweeps a whole film; the sweep kernel's single active lane
-  // takes ten times as long even where that workgroup has a thousand ordinates
+  // faces, one ordinate per group, within the kernel's registers and LDS.
+  // Iterations in us, the general kernels' and this one's: 120 cells, 96 groups
+  // FP32 30.6 and 8.0, FP64 33.0 and 7.9; 960 groups FP32 39.4 and 39.7, FP64
+  // 53.6 and 38.7; 1000 cells, 96 groups FP32 140 and 18.7, 960 groups 148 and
+  // 96.7. One workgroup sweeps a whole film, so its time goes with the groups,
+  // and in double whatever the precision: a single film in FP32 of up to 256
+  // cells with more than four groups per CU takes the general kernels where the
+  // lines fitted to such times put them first (1600 groups: 4 cells 35.4 and
+  // 56.1, 128 cells 46.9 and 61.4, 250 cells 65.1 and 71.9; 180 cells, 1050
+  // groups 50.8 and 49.0)
   h->d_film = nullptr;
   h->film_cells = 0;
   h->film_reflects = false;
@@ -839,7 +846,12 @@ bte_status build_plan_arrays(bte_ctx* h, const Plan& pl_in) {
       }
       film.push_back(f);
     }
-    ok = ok && film_lds_bytes(film_cpl(h->film_cells), n_grp_inst) <= kFilmLds;
+    const int cpl = film_cpl(h->film_cells);
+    ok = ok && film_lds_bytes(cpl, n_grp_inst) <= kFilmLds;
+    if (prec == BTE_PREC_FP32 && h->inst.size() == 1 && n_grp_inst > 4 * h->n_cu && cpl <= 4) {
+      const double per_grp = cpl == 1 ? 0.034 : cpl == 2 ? 0.038 : 0.0445;
+      ok = ok && 3.0 + per_grp * n_grp_inst <= 13.0 + 0.13 * h->film_cells + 0.0125 * n_grp_inst;
+    }
     if (ok) HIPCHK(pp.upload(&h->d_film, film));
   }
   // LDS carve-up

@@ -90,6 +90,22 @@ def test_grid_order_of_films(hip_lib):
         check(p, T, q, "fp64", 6)
 
 
+@pytest.mark.parametrize("n,n_mu,precision,count,want", [
+    (20, 64, "fp32", 1, True), (20, 100, "fp32", 1, False), (20, 100, "fp64", 1, True), (20, 100, "fp32", 2, True),
+    (130, 100, "fp32", 1, False), (256, 90, "fp32", 1, True), (500, 76, "fp32", 1, True),
+])
+def test_single_film_of_many_groups(hip_lib, n, n_mu, precision, count, want):
+    """One workgroup sweeps a film, in double: a single FP32 film with many
+    groups and few cells takes the general kernels."""
+    ps = [film(n, n_mu=n_mu, bands=15)] * count
+    s = hip_lib.BatchSolver(ps, precision=precision)
+    assert ("film" in s.paths()) == want
+    Ts, qs, _ = s.solve([torch.tensor(p.Q, device="cuda") for p in ps], tol=0.0, max_iters=5, check_every=3)
+    s.close()
+    for p, T, q in zip(ps, Ts, qs):
+        check(p, T, q, precision, 5)
+
+
 @pytest.mark.parametrize("make,plan,order,want", [
     (lambda: film(200), None, 1, True), (lambda: film(1024), None, 1, True), (lambda: film(1025), None, 1, False),
     (lambda: film(200), dict(G=2), 1, False), (lambda: film(200), None, 2, False),
