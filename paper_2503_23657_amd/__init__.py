@@ -375,7 +375,7 @@ class Solver(_Workspace):
         t = "float" if self.prec == PREC_FP32 else "double"
         if "film" in self.paths():
             cpl = next(c for c in (1, 2, 4, 8, 16) if self.problem.n[0] <= 64 * c)
-            return f"film_chunk_kernel<{t}, {cpl}, {8 if cpl == 16 else 16}>"
+            return f"film_chunk_kernel<{t}, {cpl}, {8 if cpl == 16 else 16}, true>"
         if self.problem.dim == 3 and pl["NR"] >= 1:
             return f"sweep2d_kernel<{t}, 1, {pl['NR']}, {pl['P']}, 1, 0, true>"
         if self.problem.dim == 3:

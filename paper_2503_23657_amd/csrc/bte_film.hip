@@ -52,7 +52,9 @@ __device__ __forceinline__ void compose(double& A, double& B) {
 
 enum { FC_KS, FC_CQ, FC_A, FC_IN, FC_W0, FC_W1, FC_WO, FC_DEN };
 
-template <typename T, int CPL, int NW>
+// KEEP: the iterations change the state (else they are only timed: an instance
+// that is done runs, too; a switch at run time cost films of 900 cells 3 %)
+template <typename T, int CPL, int NW, bool KEEP>
 __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
   constexpr int N = 64 * CPL, NT = NW * 64, HW = NW / 2;
   constexpr int CT = (N + NT - 1) / NT;  // cells per thread of the sums
@@ -66,8 +68,7 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
   const FinInst& F = A.fin[inst];
   const FilmInst& W = A.walls[inst];
   StatusDev* st = reinterpret_cast<StatusDev*>(I.status);
-  const bool keep = !(A.flags & FILM_TIMING);
-  if (st->done && keep) return;
+  if (KEEP && st->done) return;
   const bool adj = (A.flags & FIN_ADJ) != 0;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = I.ncell, iter = st->iter, cur = iter & 1, nxt = (iter + A.n_iter) & 1;
@@ -195,7 +196,7 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
           u = s * W.inv_half[face];
         }
         sC[(size_t)g * kFilmConst + FC_IN] = sC[(size_t)g * kFilmConst + FC_DEN] * u;
-        if (last && keep) ubf[(size_t)gi.w * I.n_bface + W.slot[face]] = (T)u;
+        if (KEEP && last) ubf[(size_t)gi.w * I.n_bface + W.slot[face]] = (T)u;
       }
     }
     __syncthreads();
@@ -209,7 +210,7 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
         if (c >= n) continue;
         const double v = total(c), m = sqrt(v * v), d = m - qm[p];
         qm[p] = m;
-        if (last && keep) {
+        if (KEEP && last) {
           F.q[c] = v;
           F.qmag_prev[c] = m;
           res[2] += d * d;
@@ -219,7 +220,7 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
       __syncthreads();
     }
   }
-  if (!keep) return;
+  if (!KEEP) return;
   // ---- the new state, in grid order and in both octants' layouts
   T* xq = reinterpret_cast<T*>(I.xq[nxt]);
   for (int c = tid; c < n; c += NT) {
@@ -259,9 +260,9 @@ __global__ void __launch_bounds__(NW * 64) film_chunk_kernel(FilmArgs A) {
   }
 }
 
-template <typename T, int CPL, int NW>
-hipError_t film_one(const FilmArgs& a, int n_inst, hipStream_t st) {
-  auto k = film_chunk_kernel<T, CPL, NW>;
+template <typename T, int CPL, int NW, bool KEEP>
+hipError_t film_launch(const FilmArgs& a, int n_inst, hipStream_t st) {
+  auto k = film_chunk_kernel<T, CPL, NW, KEEP>;
   static_assert(NW == film_waves(CPL), "the LDS a launch asks for");
   const size_t lds = film_lds_bytes(CPL, a.n_grp);
   static const hipError_t attr = hipFuncSetAttribute(
@@ -269,6 +270,12 @@ hipError_t film_one(const FilmArgs& a, int n_inst, hipStream_t st) {
   if (attr != hipSuccess || lds > (size_t)kFilmLds) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k, dim3(n_inst), dim3(NW * 64), lds, st, a);
   return hipGetLastError();
+}
+
+template <typename T, int CPL, int NW>
+hipError_t film_one(const FilmArgs& a, int n_inst, hipStream_t st) {
+  return (a.flags & FILM_TIMING) ? film_launch<T, CPL, NW, false>(a, n_inst, st)
+                                 : film_launch<T, CPL, NW, true>(a, n_inst, st);
 }
 
 template <typename T>
