@@ -887,7 +887,10 @@ bool build_schedule(const HostInst& hi, const Plan& plan, Schedule& s, std::stri
   const int nS = (nKc + LK - 1) / LK;
   const int V = nJB * W;
   int du;
-  if (R == 1) du = std::max(V, LK);
+  // 3D: a strip's first plane reads what the last plane of the strip before it
+  // wrote lag = du - (LK - 1) steps ago, and the kernel reads 8 steps (kPad2)
+  // ahead of use; narrow grids wait until twice that has passed
+  if (R == 1) du = std::max(V, LK - 1 + 2 * kPad2);
   else du = std::max(LK - 1 + C, (V + R - 1) / R);
   int T = (nS - 1) * du + V + (LJ - 1) + (LK - 1) + 1;
   T = (T + C - 1) / C * C;
